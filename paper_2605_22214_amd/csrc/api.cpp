@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "coeffs.h"
+#include "fused2d.h"
 #include "internal.h"
 
 using namespace nflbm;
@@ -95,6 +96,11 @@ struct nflbm_sim {
   bool c2c2 = false;
   void* mob = nullptr;
   void* phi = nullptr;
+  // fused D2Q9 steps (fused2d.hip): the other set of node records (v, the f
+  // record, mu~), written by every second launch; the primary arrays hold
+  // the state between calls.  Null where the runs do not qualify or the
+  // memory is not there: the steps are then taken one by one.
+  void* fused_rec = nullptr;
   bool borrowed = false; // state arrays live in caller memory (nflbm_bind_state)
   // domain-size diagnostic: batched R2C plan and its buffers (made on first use)
   hipfftHandle fft = 0;
@@ -153,6 +159,10 @@ struct nflbm_batch {
   int2* work_conc = nullptr;
   int2* work_update = nullptr;
   int blocks_conc = 0, blocks_update = 0;
+  // fused D2Q9 steps: arguments [half][launch parity][count] and the work list
+  FusedArgs* fargs = nullptr;
+  int2* work_fused = nullptr;
+  int blocks_fused = 0;
   std::vector<int> key;     // member parities that args[0..count) was built for
   std::vector<unsigned> versions;   // members' boundary_version at that build
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -240,7 +250,7 @@ void free_device(nflbm_sim* s) {
   s->out_red = nullptr;
   if (s->mob) (void)hipFree(s->mob);
   if (s->phi) (void)hipFree(s->phi);
-  s->mob = s->phi = nullptr;
+  s->mob = s->phi = s->fused_rec = nullptr;   // fused_rec lies in the params block
   if (s->fft_made) (void)hipfftDestroy(s->fft);
   s->fft_made = false;
   if (s->lam) (void)hipFree(s->lam);
@@ -550,6 +560,163 @@ int launch_step(nflbm_sim* s, hipEvent_t ev0, hipEvent_t ev1, bool* checked = nu
   return NFLBM_OK;
 }
 
+// ------------------------------------------------- fused D2Q9 steps
+// Shape of the fused launches: LDS rows of 1 << wlog2 positions, up to T
+// steps a launch, tiles of h rows.
+struct FusedPlan {
+  int wlog2, T, h, threads;
+};
+
+size_t fused_lds(const nflbm_sim* s, const FusedPlan& p) {
+  return fused_position_bytes(s->N, s->ts, s->fform != 0) * (size_t(p.h + 4 * p.T) << p.wlog2);
+}
+
+// Tile columns and rows of a lattice: tiles as even as their largest size allows.
+void fused_tiling(const FusedPlan& p, int nx, int ny, int* w, int* h, int* tx, int* ty) {
+  const int wmax = (1 << p.wlog2) - 4 * p.T;
+  *tx = (nx + wmax - 1) / wmax;
+  *w = (nx + *tx - 1) / *tx;
+  *ty = (ny + p.h - 1) / p.h;
+  *h = (ny + *ty - 1) / *ty;
+}
+
+// The shape for the simulations m[0..count) stepped together (they share N,
+// precision and record form); false if none fits LDS.  A lattice that small
+// tiles cannot spread over the chip is bound by the latency of each launch and
+// phase: few nodes a workgroup and more steps a launch.  A lattice of several
+// rounds of workgroups is bound by the work, which larger tiles and two steps
+// keep lowest (the halo recomputed per node falls with the tile, each further
+// step adds a ring of two nodes).  Per step, measured: 64 x 64 FP64 N = 3,
+// 2.96 us with 4 steps of 16 x 4 tiles against 5.3 us with 2 of 24 x 16;
+// 1100 x 1100 FP32 N = 3, 24.6 us with 2 steps of 24 x 24 against 27.3 us of
+// 24 x 8; N = 6 FP64 at 700 x 700, 48.7 us with 24 x 16 against 56.0 us.
+bool fused_plan(const nflbm_sim* const* m, size_t count, FusedPlan* out) {
+  const nflbm_sim* s = m[0];
+  const bool wide = s->store == NFLBM_FP64 && s->N >= 5;   // over 128 VGPRs
+  const FusedPlan small = wide ? FusedPlan{5, 3, 4, 512} : FusedPlan{5, 4, 4, 1024};
+  FusedPlan large = wide ? FusedPlan{5, 2, 16, 512} : FusedPlan{5, 2, 24, 1024};
+  if (s->store != NFLBM_FP64 && s->N >= 4) large.threads = 512;
+  if (!s->fform) large = FusedPlan{6, 2, 24, 1024};
+  const FusedPlan medium{5, 2, 8, 512};
+  const FusedPlan plans[] = {small, {5, 3, 8, 512}, medium, large, {5, 2, 16, 512}, medium};
+  for (int q = 0; q < 6; ++q) {
+    const FusedPlan& p = plans[q];
+    const size_t lds = fused_lds(s, p);
+    if (lds > s->lds_max) continue;
+    long long tiles = 0;
+    for (size_t i = 0; i < count; ++i) {
+      int w, h, tx, ty;
+      fused_tiling(p, m[i]->nx, m[i]->ny, &w, &h, &tx, &ty);
+      tiles += 1LL * tx * ty;
+    }
+    // one round of workgroups: one a CU (256 CUs), the medium ones two where
+    // LDS holds them; the last three are for lattices beyond that
+    const long long round = q < 2 ? 256 : (2 * lds <= s->lds_max ? 512 : 256);
+    if (q >= 3 || tiles <= round) {
+      *out = p;
+      return true;
+    }
+  }
+  return false;
+}
+
+// Whether the configuration can take fused steps at all (node records of a
+// periodic D2Q9 lattice, f as records too or not evolved), and whether it
+// can now (no solid nodes).
+bool fused_kind(const nflbm_sim* s) {
+  return s->lat == NFLBM_D2Q9 && s->gform && (s->fform || (s->step_flags & kFlagNoHydro)) && !s->wall[0] &&
+         !s->wall[1];
+}
+bool fused_now(const nflbm_sim* s) { return s->fused_rec && !s->bb && s->out_face < 0 && !s->f_local; }
+
+// Arguments of a fused launch from C set `cur`: from the primary records to
+// the others (odd = 0) or back.
+FusedArgs fused_args(const nflbm_sim* s, const FusedPlan& p, int cur, int odd) {
+  FusedArgs a{};
+  const size_t n = s->n;
+  unsigned char* o = static_cast<unsigned char*>(s->fused_rec);
+  void* rec[2][3] = {{s->mu, s->vel, s->frec}, {o, o, o}};
+  if (s->fform) {
+    rec[1][0] = o + 8 * n * s->rs;
+    rec[1][1] = o;
+    rec[1][2] = o + 4 * n * s->rs;
+  }
+  a.csrc = s->conc[cur];
+  a.cdst = s->conc[1 - cur];
+  a.mu_src = rec[odd][0];
+  a.vel_src = rec[odd][1];
+  a.frec_src = rec[odd][2];
+  a.mu_dst = rec[1 - odd][0];
+  a.vel_dst = rec[1 - odd][1];
+  a.frec_dst = rec[1 - odd][2];
+  a.nanflag = s->nanflag;
+  a.nx = s->nx;
+  a.ny = s->ny;
+  int ty;
+  fused_tiling(p, s->nx, s->ny, &a.tile_w, &a.tile_h, &a.tiles_x, &ty);
+  a.flags = s->step_flags;
+  return a;
+}
+int fused_tiles(const FusedArgs& a) { return a.tiles_x * ((a.ny + a.tile_h - 1) / a.tile_h); }
+
+hipError_t launch_fused(const nflbm_sim* s, const FusedLaunch& f, hipStream_t st) {
+  switch (s->store) {
+    case NFLBM_FP64: return launch_fused2d_0(s->N, f, st);
+    case NFLBM_FP32: return launch_fused2d_1(s->N, f, st);
+    default: return launch_fused2d_2(s->N, f, st);
+  }
+}
+
+// An even number of launches for n >= 2 steps, so that the state ends in the
+// primary records: launch i takes fused_count(n, launches, i) steps.
+long long fused_launches(long long n, int T) { return 2 * ((n + 2 * T - 1) / (2 * T)); }
+int fused_count(long long n, long long launches, long long i) {
+  return static_cast<int>(n / launches + (i < n % launches ? 1 : 0));
+}
+
+// n steps of s on its stream; *checked is set when one of them checked for
+// non-finite values.
+int run_steps(nflbm_sim* s, long long n, bool* checked) {
+  for (; n > 0 && s->f_local; --n) {
+    const int rc = launch_step(s, nullptr, nullptr, checked);
+    if (rc != NFLBM_OK) return rc;
+  }
+  FusedPlan p;
+  if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p)) {
+    if (fused_launches(n, p.T) > n) {      // one step a launch, an odd number
+      const int rc = launch_step(s, nullptr, nullptr, checked);
+      if (rc != NFLBM_OK) return rc;
+      --n;
+    }
+    const FusedArgs a[2] = {fused_args(s, p, s->cur, 0), fused_args(s, p, s->cur ^ 1, 1)};
+    FusedLaunch f{};
+    f.params = s->params;
+    f.frecord = s->fform;
+    f.wlog2 = p.wlog2;
+    f.threads = p.threads;
+    f.blocks = fused_tiles(a[0]);
+    f.lds = fused_lds(s, p);
+    const long long launches = fused_launches(n, p.T);
+    for (long long i = 0; i < launches; ++i) {
+      f.one = &a[i & 1];
+      f.nsteps = fused_count(n, launches, i);
+      f.nanmask = 0;
+      for (int t = 0; t < f.nsteps; ++t) {
+        ++s->step_count;
+        if (s->nan_every > 0 && s->step_count % s->nan_every == 0) f.nanmask |= 1u << t;
+      }
+      if (f.nanmask) *checked = true;
+      HIPCHK(s, launch_fused(s, f, s->stream));
+    }
+    return NFLBM_OK;
+  }
+  for (; n > 0; --n) {
+    const int rc = launch_step(s, nullptr, nullptr, checked);
+    if (rc != NFLBM_OK) return rc;
+  }
+  return NFLBM_OK;
+}
+
 // Host copy of a NaN flag behind the work queued so far on stream.
 hipError_t nan_enqueue(int* dev, int* host, hipEvent_t ev, hipStream_t stream) {
   hipError_t e = hipMemcpyAsync(host, dev, sizeof(int), hipMemcpyDeviceToHost, stream);
@@ -730,8 +897,20 @@ void free_batch_tables(nflbm_batch* b) {
   if (b->args) (void)hipFree(b->args);
   if (b->work_conc) (void)hipFree(b->work_conc);
   if (b->work_update) (void)hipFree(b->work_update);
+  if (b->fargs) (void)hipFree(b->fargs);
+  if (b->work_fused) (void)hipFree(b->work_fused);
   b->args = nullptr;
+  b->fargs = nullptr;
+  b->work_fused = nullptr;
+  b->blocks_fused = 0;
   b->work_conc = b->work_update = nullptr;
+}
+
+// Whether every member can take fused steps, all in one record form.
+bool fused_batch(const nflbm_batch* b) {
+  for (const nflbm_sim* m : b->members)
+    if (!m->fused_rec || m->bb || m->out_face >= 0 || m->fform != b->members[0]->fform) return false;
+  return true;
 }
 
 // (Re)build the work lists and the step arguments of both parities for the
@@ -781,6 +960,35 @@ int build_batch_tables(nflbm_batch* b, bool new_shape) {
     b->blocks_update = static_cast<int>(wu.size());
   }
   BHIPCHK(b, hipMemcpyAsync(b->args, args.data(), args.size() * sizeof(StepArgs), hipMemcpyHostToDevice, b->stream));
+  std::vector<FusedArgs> fa;
+  std::vector<int2> wf;
+  FusedPlan p;
+  if (fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+    for (int q = 0; q < 4; ++q)      // half q >> 1, launch parity q & 1
+      for (int i = 0; i < count; ++i) {
+        const nflbm_sim* m = b->members[i];
+        fa.push_back(fused_args(m, p, m->cur ^ (q >> 1) ^ (q & 1), q & 1));
+        fa.back().nanflag = b->nanflag;
+        for (int t = 0; q == 0 && t < fused_tiles(fa.back()); ++t) wf.push_back(make_int2(i, t));
+      }
+    if (b->blocks_fused != static_cast<int>(wf.size())) {
+      if (b->fargs) (void)hipFree(b->fargs);
+      if (b->work_fused) (void)hipFree(b->work_fused);
+      b->fargs = nullptr;
+      b->work_fused = nullptr;
+      b->blocks_fused = 0;
+      if (hipMalloc(reinterpret_cast<void**>(&b->fargs), fa.size() * sizeof(FusedArgs)) == hipSuccess &&
+          hipMalloc(reinterpret_cast<void**>(&b->work_fused), wf.size() * sizeof(int2)) == hipSuccess) {
+        b->blocks_fused = static_cast<int>(wf.size());
+      } else {
+        (void)hipGetLastError();      // the steps are then taken one by one
+      }
+    }
+    if (b->blocks_fused) {
+      BHIPCHK(b, hipMemcpyAsync(b->fargs, fa.data(), fa.size() * sizeof(FusedArgs), hipMemcpyHostToDevice, b->stream));
+      BHIPCHK(b, hipMemcpyAsync(b->work_fused, wf.data(), wf.size() * sizeof(int2), hipMemcpyHostToDevice, b->stream));
+    }
+  }
   BHIPCHK(b, hipMemcpyAsync(b->work_conc, wc.data(), wc.size() * sizeof(int2), hipMemcpyHostToDevice, b->stream));
   BHIPCHK(b, hipMemcpyAsync(b->work_update, wu.data(), wu.size() * sizeof(int2), hipMemcpyHostToDevice, b->stream));
   BHIPCHK(b, hipStreamSynchronize(b->stream));
@@ -922,6 +1130,34 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
   int half = 0;
   int rc = batch_half(b, &half);
   if (rc != NFLBM_OK) return rc;
+  FusedPlan p;
+  if (nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+    const nflbm_sim* m0 = b->members[0];
+    FusedLaunch f{};
+    f.params = b->params;
+    f.work = b->work_fused;
+    f.frecord = m0->fform;
+    f.wlog2 = p.wlog2;
+    f.threads = p.threads;
+    f.blocks = b->blocks_fused;
+    f.lds = fused_lds(m0, p);
+    if (fused_launches(nsteps, p.T) > nsteps) {   // one step a launch, an odd number
+      BHIPCHK(b, launch_half(b, half));
+      for (nflbm_sim* m : b->members) m->cur ^= 1;
+      half ^= 1;
+      --nsteps;
+    }
+    const long long launches = fused_launches(nsteps, p.T);
+    for (long long i = 0; i < launches; ++i) {
+      f.batch = b->fargs + (2 * size_t(half) + size_t(i & 1)) * b->members.size();
+      f.nsteps = fused_count(nsteps, launches, i);
+      f.nanmask = ~0u;
+      BHIPCHK(b, launch_fused(m0, f, b->stream));
+    }
+    BHIPCHK(b, nan_enqueue(b->nanflag, b->nan_host, b->nan_ev, b->stream));
+    b->nan_pending = true;
+    return NFLBM_OK;
+  }
   long long t = 0;
   if (mode == NFLBM_BATCH_GRAPH) {
     const long long reps = nsteps / b->graph_steps;
@@ -1311,7 +1547,19 @@ int nflbm_create(const nflbm_config* cfg, nflbm_sim** out) {
   bool ok = hipGetDevice(&s->device) == hipSuccess;
   for (auto& a : state_arrays(s)) ok = ok && hipMalloc(a.first, a.second) == hipSuccess;
   const size_t psize = s->ts == 8 ? sizeof(DevParams<double>) : sizeof(DevParams<float>);
-  ok = ok && hipMalloc(&s->params, psize) == hipSuccess;
+  // the other record set of the fused steps lies behind the tables (one
+  // allocation less); without room for it the steps are taken one by one
+  FusedPlan fplan;
+  if (ok && fused_kind(s) && fused_plan(&s, 1, &fplan)) {
+    const size_t bytes = align_up(psize) + ((s->fform ? 8 : 0) + size_t(s->NE)) * n * s->rs;
+    if (hipMalloc(&s->params, bytes) == hipSuccess) {
+      s->fused_rec = static_cast<unsigned char*>(s->params) + align_up(psize);
+    } else {
+      s->params = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  ok = ok && (s->params || hipMalloc(&s->params, psize) == hipSuccess);
   ok = ok && hipMalloc(reinterpret_cast<void**>(&s->nanflag), sizeof(int)) == hipSuccess;
   ok = ok && hipHostMalloc(reinterpret_cast<void**>(&s->nan_host), sizeof(int), hipHostMallocDefault) == hipSuccess;
   ok = ok && hipEventCreateWithFlags(&s->nan_ev, hipEventDisableTiming) == hipSuccess;
@@ -1656,10 +1904,8 @@ int nflbm_step(nflbm_sim* sim, long long nsteps) {
   int rc = sim_nan_status(sim, false);
   if (rc != NFLBM_OK) return rc;
   bool checked = false;
-  for (long long t = 0; t < nsteps; ++t) {
-    rc = launch_step(sim, nullptr, nullptr, &checked);
-    if (rc != NFLBM_OK) return rc;
-  }
+  rc = run_steps(sim, nsteps, &checked);
+  if (rc != NFLBM_OK) return rc;
   if (checked) {
     // the device flag only ever goes from 0 to 1, so a newer copy subsumes
     // one still in flight; the event follows the newest
@@ -1700,9 +1946,12 @@ int nflbm_step_timed(nflbm_sim* sim, long long nsteps, double* ms, double* ms_up
   if (rc0 != NFLBM_OK) return rc0;
   bool checked = false;
   HIPCHK(sim, hipEventRecord(e0, sim->stream));
-  for (long long t = 0; t < nsteps; ++t) {
-    const int rc = ms_update ? launch_step(sim, ev[2 * t], ev[2 * t + 1], &checked)
-                             : launch_step(sim, nullptr, nullptr, &checked);
+  if (!ms_update) {
+    const int rc = run_steps(sim, nsteps, &checked);
+    if (rc != NFLBM_OK) return rc;
+  }
+  for (long long t = 0; ms_update && t < nsteps; ++t) {
+    const int rc = launch_step(sim, ev[2 * t], ev[2 * t + 1], &checked);
     if (rc != NFLBM_OK) return rc;
   }
   HIPCHK(sim, hipEventRecord(e1, sim->stream));

@@ -1,0 +1,94 @@
+"""Fused D2Q9 steps: several steps in one launch equal the same steps taken
+one call at a time (the two-kernel path) bit for bit, in every form, for
+tiles of every shape the plan chooses and lattices smaller than their halo."""
+import numpy as np
+import pytest
+
+import paper_2605_22214_amd as nf
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("C", "V", "P", "F", "MU")
+PLAIN, DIFF, POT = 0, nf.FLAG_NO_HYDRO, nf.FLAG_POTENTIAL_FORCE
+
+
+def _config(shape, N, precision, flags=0, omega=0.0, force=(0.0, 0.0, 0.0)):
+    return dict(lattice="D2Q9", shape=shape + (1,), sigma=0.01 * (np.ones((N, N)) - np.eye(N)), tau=np.ones(N),
+                m=0.05, precision=precision, flags=flags, omega_stab=omega, body_force=force)
+
+
+def _noise(shape, N, seed):
+    C = 1.0 / N + np.random.default_rng(seed).uniform(-0.1, 0.1, size=(N, 1, shape[1], shape[0]))
+    return C / C.sum(axis=0)
+
+
+def _same(a, b):
+    for name in FIELDS:
+        assert np.array_equal(a.get_field(name), b.get_field(name)), name
+    assert np.array_equal(a.get_state(), b.get_state())
+
+
+CASES = [
+    ((64, 64), 3, "fp64", PLAIN, 0.0, (0.0, 0.0, 0.0)),        # small tiles, four steps a launch
+    ((5, 3), 2, "fp32", PLAIN, 0.0, (0.0, 0.0, 1e-6)),         # smaller than the halo
+    ((1, 1), 3, "fp32", PLAIN, 0.0, (0.0, 0.0, 0.0)),
+    ((161, 150), 4, "fp32", PLAIN, 0.05, (1e-5, 0.0, 0.0)),    # 20 x 8 tiles
+    ((250, 253), 4, "fp16s", PLAIN, 0.0, (0.0, 1e-6, 0.0)),    # 24 x 8
+    ((515, 389), 3, "fp32", POT, 0.0, (0.0, 0.0, 0.0)),        # 24 x 24, 1024 threads
+    ((419, 470), 5, "fp16s", POT, 0.05, (0.0, 0.0, 0.0)),      # 24 x 24, 512 threads
+    ((301, 150), 6, "fp64", PLAIN, 0.05, (0.0, 0.0, 0.0)),     # 24 x 16
+    ((170, 333), 8, "fp64", PLAIN, 0.0, (0.0, 0.0, 0.0)),      # the largest records
+    ((90, 33), 7, "fp32", PLAIN, 0.0, (0.0, 0.0, 0.0)),
+    ((700, 433), 4, "fp32", DIFF, 0.05, (0.0, 0.0, 0.0)),      # 56 x 24
+    ((90, 33), 3, "fp64", DIFF, 0.0, (0.0, 0.0, 0.0)),
+    ((433, 250), 5, "fp16s", DIFF, 0.0, (0.0, 0.0, 0.0)),
+    ((3, 70), 8, "fp64", DIFF, 0.05, (0.0, 0.0, 0.0)),
+]
+
+
+@pytest.mark.parametrize("shape,N,precision,flags,omega,force", CASES)
+def test_fused_equals_single_steps(shape, N, precision, flags, omega, force):
+    cfg = _config(shape, N, precision, flags, omega, force)
+    a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+    C = _noise(shape, N, 1)
+    a.set_fields(C)
+    b.set_fields(C)
+    for _ in range(15):
+        a.step(1)
+    b.step(1)
+    b.step(2)
+    b.step(3)
+    b.step(9)
+    _same(a, b)
+
+
+@pytest.mark.parametrize("precision,flags", [("fp32", PLAIN), ("fp64", PLAIN), ("fp32", DIFF)])
+def test_fused_batch_equals_single_steps(precision, flags):
+    shapes = [(64, 41), (130, 97), (7, 200), (33, 33)]
+    cfgs = [_config(s, 3, precision, flags, 0.05 * (i & 1)) for i, s in enumerate(shapes)]
+    batch = nf.Batch(cfgs)
+    sims = [nf.Simulation(**c) for c in cfgs]
+    for i, s in enumerate(shapes):
+        batch.set_fields(i, _noise(s, 3, i))
+        sims[i].set_fields(_noise(s, 3, i))
+    for n in (1, 7, 1, 12):
+        batch.step(n)
+        for s in sims:
+            for _ in range(n):
+                s.step(1)
+    for m, s in zip(batch.members, sims):
+        _same(m, s)
+
+
+def test_fused_steps_report_nan():
+    cfg = _config((70, 50), 3, "fp32")
+    s = nf.Simulation(**cfg)
+    C = _noise((70, 50), 3, 2)
+    C[0, 0, 20, 30] = np.nan
+    s.set_fields(C)
+    s.set_nan_check(5)
+    s.step(3)
+    s.synchronize()          # no checked step yet
+    s.step(4)                # the fifth is
+    with pytest.raises(nf.NflbmError):
+        s.synchronize()
