@@ -1,0 +1,37 @@
+"""Read-back of fields large enough for the staged copy: every value arrives
+at its place, also from two threads reading two simulations."""
+import threading
+
+import numpy as np
+import pytest
+
+import paper_2605_22214_amd as nf
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape", [(128, 128, 86), (130, 127, 85), (200, 120, 111)])
+def test_large_fields_read_back_whole(shape):
+    # C of the initial state is the set one exactly (no flow, mu~ = 0)
+    assert 3 * np.prod(shape) * 8 > 32 << 20
+    sims, fields, out = [], [], [None, None]
+    for seed in range(2):
+        s = nf.Simulation("D3Q19", shape, 0.01 * (np.ones((3, 3)) - np.eye(3)), np.ones(3), m=0.05)
+        C = np.random.default_rng(seed).uniform(0.1, 0.4, size=(3,) + shape[::-1])
+        C[2] = 1.0 - C[0] - C[1]
+        s.set_fields(C)
+        sims.append(s)
+        fields.append(C)
+
+    def read(i):
+        for _ in range(3):
+            out[i] = sims[i].get_field("C")
+
+    threads = [threading.Thread(target=read, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for C, got in zip(fields, out):
+        assert np.array_equal(got[:2], C[:2])
+        assert np.array_equal(got[2], 1.0 - (C[0] + C[1]))
