@@ -99,7 +99,8 @@ struct nflbm_sim {
   void* out_buf = nullptr;
   double* out_red = nullptr;
   int out_blocks = 0;
-  // solid geometry: per-node pull masks (StepArgs::bb) and the caller's mask
+  // solid geometry: per-node pull masks (StepArgs::bb), behind them the entering
+  // directions across open faces (StepArgs::ob), and the caller's mask
   uint32_t* bb = nullptr;
   std::vector<unsigned char> solid_host;
   // concentration-dependent mobility: MobParams and the potential scratch
@@ -439,6 +440,7 @@ StepArgs make_args(const nflbm_sim* s, int src) {
   a.params = s->params;
   a.bb = s->bb;
   a.faces = s->faces;
+  a.ob = s->bb ? s->bb + s->n : nullptr;
   a.out_face = s->out_face;
   if (s->out_face >= 0) {
     const size_t P = s->out_plane;
@@ -1548,12 +1550,23 @@ std::vector<std::pair<void**, size_t>> state_arrays(nflbm_sim* s) {
   return v;
 }
 
-// The device table of the open and outflow faces (freed when there is none).
+// The map of entering directions for the walls, solid nodes and open faces
+// as they are now; without solid nodes the kernels form it from the faces.
+int build_open_map(nflbm_sim* sim) {
+  const int open = sim->open_mask | (sim->out_face >= 0 ? 1 << sim->out_face : 0);
+  if (!open || !sim->bb) return NFLBM_OK;
+  HIPCHK(sim, launch_build_ob(sim->lat, open, sim->bb + sim->n, make_args(sim, sim->cur), sim->stream));
+  HIPCHK(sim, hipStreamSynchronize(sim->stream));
+  return NFLBM_OK;
+}
+
+// The device table of the open and outflow faces (freed when there is none),
+// and their map.
 int upload_faces(nflbm_sim* sim) {
   if (!sim->open_mask && sim->out_face < 0) {
     if (sim->faces) (void)hipFree(sim->faces);
     sim->faces = nullptr;
-    return NFLBM_OK;
+    return build_open_map(sim);
   }
   const size_t bytes = sim->ts == 8 ? sizeof(FaceBC<double>) : sizeof(FaceBC<float>);
   if (!sim->faces && hipMalloc(&sim->faces, bytes) != hipSuccess) {
@@ -1573,7 +1586,7 @@ int upload_faces(nflbm_sim* sim) {
     delete t;
   }
   if (e != hipSuccess) return hip_fail(sim, e, "set_open_face");
-  return NFLBM_OK;
+  return build_open_map(sim);
 }
 
 constexpr size_t kBindAlign = 256;
@@ -1918,7 +1931,7 @@ int nflbm_set_solid(nflbm_sim* sim, const unsigned char* solid) {
   size_t fluid = 0;
   for (size_t q = 0; q < n; ++q) fluid += solid[q] ? 0 : 1;
   if (fluid == 0) return fail(sim, NFLBM_EINVAL, "every node is solid");
-  if (!sim->bb && hipMalloc(reinterpret_cast<void**>(&sim->bb), n * sizeof(uint32_t)) != hipSuccess) {
+  if (!sim->bb && hipMalloc(reinterpret_cast<void**>(&sim->bb), 2 * n * sizeof(uint32_t)) != hipSuccess) {
     sim->bb = nullptr;
     return fail(sim, NFLBM_ENOMEM, "cannot allocate the solid geometry");
   }
@@ -1933,7 +1946,9 @@ int nflbm_set_solid(nflbm_sim* sim, const unsigned char* solid) {
   sim->solid_host.assign(solid, solid + n);
   sim->out_fluid = fluid_out;
   {
-    const int rc = refresh_outflow_plane(sim);
+    int rc = build_open_map(sim);
+    if (rc) return rc;
+    rc = refresh_outflow_plane(sim);
     if (rc) return rc;
     HIPCHK(sim, hipStreamSynchronize(sim->stream));
   }

@@ -372,6 +372,77 @@ __device__ __forceinline__ bool pulled_from_wall(const Nbr& b, int k) {
   if (!WALLS) return false;
   return (b.pm >> k) & 1u;
 }
+// Pull bits of the directions that enter across face fc (0..5).
+template <class L>
+__host__ __device__ constexpr uint32_t face_pulls(int fc) {
+  uint32_t m = 0u;
+  for (int k = 1; k < L::Q; ++k)
+    if (L::e[k][fc >> 1] == ((fc & 1) ? -1 : 1)) m |= 1u << k;
+  return m;
+}
+// Component d of e_k for a k known only at run time: two bits a direction of
+// one constant, no table in memory.
+template <class L>
+__host__ __device__ constexpr unsigned long long dir_bits(int d) {
+  unsigned long long m = 0ull;
+  for (int k = 0; k < L::Q; ++k) m |= static_cast<unsigned long long>(L::e[k][d] + 1) << (2 * k);
+  return m;
+}
+template <class L>
+__device__ __forceinline__ int dir_comp(int k, int d) {
+  const unsigned long long m = d == 0 ? dir_bits<L>(0) : (d == 1 ? dir_bits<L>(1) : dir_bits<L>(2));
+  return static_cast<int>(m >> (2 * k) & 3u) - 1;
+}
+// Pull masks of a node: pm has bit k set when the population arriving along
+// e_k comes from beyond a wall face or from a solid node (bit 0: the node is
+// solid), wl only where that link is a wall, not an entry across an open
+// face (a link that also crosses a wall face, or continues a solid node, is a
+// wall link).  With solid geometry both are as stored; otherwise they follow
+// from the faces, those of x and y once per column.
+struct Pulls {
+  uint32_t pm, wl;
+};
+template <class L>
+__device__ __forceinline__ void add_face(Pulls& m, int fc, int open) {
+  m.pm |= face_pulls<L>(fc);
+  if (!(open >> fc & 1)) m.wl |= face_pulls<L>(fc);
+}
+template <class L>
+__device__ __forceinline__ Pulls column_pulls(const StepArgs& a, int open, int x, int y) {
+  Pulls m{0u, 0u};
+  if (a.wall_x && x == 0) add_face<L>(m, 0, open);
+  if (a.wall_x && x == a.nx - 1) add_face<L>(m, 1, open);
+  if (a.wall_y && y == 0) add_face<L>(m, 2, open);
+  if (a.wall_y && y == a.ny - 1) add_face<L>(m, 3, open);
+  return m;
+}
+template <class L>
+__device__ __forceinline__ Pulls node_pulls(const StepArgs& a, int open, Pulls column, int x, int y, int z) {
+  if (a.bb) {
+    const uint32_t node = uint32_t(x) + uint32_t(a.nx) * (uint32_t(y) + uint32_t(a.ny) * uint32_t(z));
+    const uint32_t pm = a.bb[node];
+    return {pm, open ? pm & ~a.ob[node] : pm};
+  }
+  if (L::DIM == 3 && a.wall_z) {
+    if (z == 0) add_face<L>(column, 4, open);
+    if (z == a.nz - 1) add_face<L>(column, 5, open);
+  }
+  return column;
+}
+// The open face across which the population along e_k enters node (x, y, z),
+// for a direction of its StepArgs::ob mask: between two, the first axis's.
+template <class L>
+__device__ __forceinline__ int open_entry(const StepArgs& a, int open, int x, int y, int z, int k) {
+  const int c[3] = {x, y, z}, n[3] = {a.nx, a.ny, a.nz}, w[3] = {a.wall_x, a.wall_y, a.wall_z};
+  int face = 0;
+#pragma unroll
+  for (int d = 2; d >= 0; --d) {
+    const int e = dir_comp<L>(k, d);
+    if (w[d] && e > 0 && c[d] == 0 && (open >> (2 * d) & 1)) face = 2 * d;
+    if (w[d] && e < 0 && c[d] == n[d] - 1 && (open >> (2 * d + 1) & 1)) face = 2 * d + 1;
+  }
+  return face;
+}
 // True when the population arriving along e_k comes from beyond a face of
 // the lattice (a walled axis), open or not.
 template <class L>

@@ -127,6 +127,9 @@ struct StepArgs {
   // beyond a wall face, bit 0 set at solid nodes themselves.
   const NFLBM_GLOBAL uint32_t* bb;
   const NFLBM_GLOBAL void* faces;     // FaceBC<T> when some face is open, else null
+  // Open faces and solid nodes (null without both): per node, bit k set when the population
+  // arriving along e_k enters across an open or outflow face (entry_face)
+  const NFLBM_GLOBAL uint32_t* ob;
   // Convective outflow face (-1 none): post-streaming populations of its
   // boundary plane, f [k-1][p] and g [i][k][p] (all k), and the ghost values
   // beyond it, C [i][p] and E_B [NE][p], compute precision, p the in-plane index
@@ -275,6 +278,9 @@ size_t update_lds_bytes(int lat, int nc, int store, int tx_log2);
 // and the wall faces of a.
 hipError_t launch_build_bb(int lat, const unsigned char* solid, uint32_t* bb, const StepArgs& a,
                            hipStream_t s);
+// The entering directions of StepArgs::ob, from the walls, solid nodes and
+// open faces (bit f of open: face f) of a.
+hipError_t launch_build_ob(int lat, int open, uint32_t* ob, const StepArgs& a, hipStream_t s);
 hipError_t launch_outflow(int lat, int nc, int store, const OutflowArgs& o, hipStream_t s);
 hipError_t launch_mob_potentials(int lat, int nc, int store, const MobArgs& a, hipStream_t s);
 hipError_t launch_mob_source(int lat, int nc, int store, const MobArgs& a, hipStream_t s);

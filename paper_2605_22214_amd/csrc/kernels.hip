@@ -259,44 +259,71 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
   // for a plane beyond a wall face (nothing is loaded).  Positions inside a
   // wall stay unfilled: a population pulled from a wall is this node's own,
   // so they are never read.
-  auto load_plane = [&](int gz) -> bool {
-    T* base = sm;
+  struct Fill {
+    T cc[NEP], mm[NEP], vv[4], ff[4];
+  };
+  auto fetch = [&](uint32_t node, Fill& f) {
+#pragma unroll
+    for (int e = NE; e < NEP; ++e) f.cc[e] = f.mm[e] = T(0);
+    vld<T, NE>(at(cprev, node * NE), reinterpret_cast<T(&)[NE]>(f.cc));
+    rec_load<S, NE>(a.mu, node * NE, reinterpret_cast<T(&)[NE]>(f.mm), T(S::mu_scale));
+    rec_load<S, 4>(a.vel, node * 4, f.vv, T(S::vel_scale));
+    if constexpr (FR) rec_load<S, 4>(a.frec, node * 4, f.ff, T(S::vel_scale));
+  };
+  auto put = [&](int idx, const Fill& f) {
+    if constexpr (AOS) {
+      T* rec = sm + idx * REC;
+      vst<T, NEP>(rec, f.cc);
+      vst<T, NEP>(rec + NEP, f.mm);
+      vst<T, 4>(rec + 2 * NEP, f.vv);
+      if constexpr (FR) vst<T, 4>(rec + 2 * NEP + 4, f.ff);
+    } else {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        sm[e * PXY + idx] = f.cc[e];
+        sm[(NE + e) * PXY + idx] = f.mm[e];
+      }
+#pragma unroll
+      for (int d = 0; d < 4; ++d) sm[(2 * NE + d) * PXY + idx] = f.vv[d];
+      if constexpr (FR) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) sm[(NF + d) * PXY + idx] = f.ff[d];
+      }
+    }
+  };
+  // the plane's offset, or false beyond a wall face
+  auto plane_offset = [&](int gz, uint32_t& zoff) -> bool {
     if (gz < 0 || gz >= a.nz) {
       if (WALLS && a.wall_z) return false;
       gz = (gz < 0) ? gz + a.nz : gz - a.nz;
     }
-    const uint32_t zoff = uint32_t(gz) * nxy;
+    zoff = uint32_t(gz) * nxy;
+    return true;
+  };
+  auto fetch_plane = [&](int gz, Fill (&nxt)[2]) -> bool {
+    uint32_t zoff;
+    if (!plane_offset(gz, zoff)) return false;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      if (fill_ok[r]) fetch(fill_off[r] + zoff, nxt[r]);
+    return true;
+  };
+  auto put_plane = [&](const Fill (&nxt)[2]) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+      if (fill_ok[r]) put(tid + 256 * r, nxt[r]);
+  };
+  // one position after the other: with both in flight the periodic kernel
+  // measured 0.346 against 0.325 ms (256^3, N = 5, FP32)
+  auto load_plane = [&](int gz) -> bool {
+    uint32_t zoff;
+    if (!plane_offset(gz, zoff)) return false;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
       if (!fill_ok[r]) continue;
-      const int idx = tid + 256 * r;
-      const uint32_t node = fill_off[r] + zoff;
-      T cc[NEP], mm[NEP], vv[4], ff[4];
-#pragma unroll
-      for (int e = NE; e < NEP; ++e) cc[e] = mm[e] = T(0);
-      vld<T, NE>(at(cprev, node * NE), reinterpret_cast<T(&)[NE]>(cc));
-      rec_load<S, NE>(a.mu, node * NE, reinterpret_cast<T(&)[NE]>(mm), T(S::mu_scale));
-      rec_load<S, 4>(a.vel, node * 4, vv, T(S::vel_scale));
-      if constexpr (FR) rec_load<S, 4>(a.frec, node * 4, ff, T(S::vel_scale));
-      if constexpr (AOS) {
-        T* rec = base + idx * REC;
-        vst<T, NEP>(rec, cc);
-        vst<T, NEP>(rec + NEP, mm);
-        vst<T, 4>(rec + 2 * NEP, vv);
-        if constexpr (FR) vst<T, 4>(rec + 2 * NEP + 4, ff);
-      } else {
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-          base[e * PXY + idx] = cc[e];
-          base[(NE + e) * PXY + idx] = mm[e];
-        }
-#pragma unroll
-        for (int d = 0; d < 4; ++d) base[(2 * NE + d) * PXY + idx] = vv[d];
-        if constexpr (FR) {
-#pragma unroll
-          for (int d = 0; d < 4; ++d) base[(NF + d) * PXY + idx] = ff[d];
-        }
-      }
+      Fill f;
+      fetch(fill_off[r] + zoff, f);
+      put(tid + 256 * r, f);
     }
     return true;
   };
@@ -345,7 +372,7 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
   struct Acc {
     T s[NE], sd[NE], c[NE], d0[NE];
     T fm, jm[3];
-    bool solid;
+    Pulls pl;        // the target's pull masks (walls)
   };
   auto zero_acc = [&](Acc& A) {
 #pragma unroll
@@ -353,7 +380,7 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
     A.fm = T(0);
 #pragma unroll
     for (int d = 0; d < 3; ++d) A.jm[d] = T(0);
-    A.solid = false;
+    A.pl = {0u, 0u};
   };
   auto add_f_value = [&](Acc& A, T fk, int kin) {
     A.fm += fk;
@@ -449,20 +476,37 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
   const T* corner = sm + (li - PX - 1) * PSTEP;
   auto src_at = [&](int ex, int ey) { return corner + ((1 - ey) * PX + (1 - ex)) * PSTEP; };
 
+  Pulls pm_xy{0u, 0u};
+  if constexpr (WALLS) pm_xy = column_pulls<L>(a, open, x, y);
+  auto pull_masks = [&](int z) -> Pulls {
+    if (!WALLS || !active || z >= z1) return {0u, 0u};
+    return node_pulls<L>(a, open, pm_xy, x, y, z);
+  };
+
   // The populations held in plane p reach three targets of this column: the
   // node of plane p + 1 (directions with e_z = +1), the node of plane p
   // itself (in-plane directions, its rest population, and every population
   // bounced back at a wall, which is its own), and the node of plane p - 1
   // (e_z = -1).  A target is complete once plane t + 1 has been seen.
+  // A wavefront of solid targets gathers nothing for them.
+  // FP64 in D3Q19: the scheduler moves nothing across a direction, or it reads
+  // so many records ahead that two wavefronts fill a SIMD's registers (210
+  // VGPRs, with the fences 152 and three wavefronts: 90.8 -> 86.7 us over
+  // 128 x 120 x 99, N = 5; the update's pairs 67.8 -> 66.4 us).
+  auto fp64_fence = [] {
+    if constexpr (D3 && sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
+  };
   auto plane_step = [&](int p, bool have, Acc& lo, Acc& mid, Acc& hi, auto WF) {
     const NFLBM_CONST DevParams<T>& P = *fresh_const(P0);
     const T negm = -P.m;
-    const bool need_hi = D3 && have && p + 1 >= z0 && p + 1 < z1;
-    const bool need_lo = D3 && have && p - 1 >= z0 && p - 1 < z1;
+    auto fluid = [](const Acc& A) { return !WALLS || __any(!(A.pl.pm & 1u)); };
+    const bool need_hi = D3 && have && p + 1 >= z0 && p + 1 < z1 && fluid(hi);
+    const bool need_lo = D3 && have && p - 1 >= z0 && p - 1 < z1 && fluid(lo);
     // Away from walls, the node of plane p + 1 (directions (ex, ey, +1)) and
     // the node of plane p - 1 (directions (ex, ey, -1)) pull from the same
     // five positions of plane p: each record is read once for both.
     const bool merged = D3 && !WALLS && need_hi && need_lo;
+    auto blocked = [](const Acc& A, int k) { return WALLS && (A.pl.pm >> k & 1u); };
     if (merged) {
 #pragma unroll
       for (int k = 1; k < Q; ++k)
@@ -472,18 +516,15 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
           read_rec(src_at(L::e[k][0], L::e[k][1]), R, WF);
           acc_rec(hi, R, k, k, WF, negm, std::false_type{});
           acc_rec(lo, R, km, km, WF, negm, std::false_type{});
+          fp64_fence();
         }
     }
     if (!merged && need_hi) {
-      const Nbr nb = neighbours<L, WALLS>(x, y, p + 1, a);
 #pragma unroll
       for (int k = 1; k < Q; ++k)
-        if (L::e[k][2] == 1 && !pulled_from_wall<L, WALLS>(nb, k))
-          add_source(hi, src_at(L::e[k][0], L::e[k][1]), k, k, WF, negm);
+        if (L::e[k][2] == 1 && !blocked(hi, k)) add_source(hi, src_at(L::e[k][0], L::e[k][1]), k, k, WF, negm);
     }
-    if (p >= z0 && p < z1) {
-      const Nbr nb = neighbours<L, WALLS>(x, y, p, a);
-      mid.solid = solid_node<WALLS>(nb);
+    if (p >= z0 && p < z1 && fluid(mid)) {
       const T* own = src_at(0, 0);
       {
         T cs[NEP], ms[NEP], v4[4];
@@ -500,12 +541,12 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
       }
 #pragma unroll
       for (int k = 1; k < Q; ++k) {
-        if (pulled_from_wall<L, WALLS>(nb, k)) {
-          const int fc = entry_face<L, WALLS>(nb, k, open);
-          if (WALLS && fc >= 0) add_open(mid, own, k, fc, WF, negm);
-          else add_source(mid, own, opposite(k), k, WF, negm);
+        if (blocked(mid, k)) {
+          if (mid.pl.wl >> k & 1u) add_source(mid, own, opposite(k), k, WF, negm);
+          else add_open(mid, own, k, open_entry<L>(a, open, x, y, p, k), WF, negm);
         } else if (L::e[k][2] == 0) {
           add_source(mid, src_at(L::e[k][0], L::e[k][1]), k, k, WF, negm);
+          if (!WALLS) fp64_fence();
         }
       }
       if constexpr (FR && !decltype(WF)::value) {
@@ -520,12 +561,11 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
     if (!merged && need_lo) {
       // in the merged path's order (by the (ex, ey, +1) directions), so that
       // a node's sums do not depend on where the z runs start and end
-      const Nbr nb = neighbours<L, WALLS>(x, y, p - 1, a);
 #pragma unroll
       for (int k = 1; k < Q; ++k)
         if (L::e[k][2] == 1) {
           const int km = direction_of<L>(L::e[k][0], L::e[k][1], -1);
-          if (!pulled_from_wall<L, WALLS>(nb, km)) add_source(lo, src_at(L::e[k][0], L::e[k][1]), km, km, WF, negm);
+          if (!blocked(lo, km)) add_source(lo, src_at(L::e[k][0], L::e[k][1]), km, km, WF, negm);
         }
     }
   };
@@ -542,8 +582,8 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
     // (every k) are the plane buffers, from which the outflow kernel that
     // wrote them (after the previous step, or when the state or the outflow
     // was set) has already formed this node's C, E_B and f moments
-    if (WALLS && !A.solid && a.out_face >= 0 && outflow_plane_index(a.out_face, 0, x, y, z, a) >= 0) return;
-    if (A.solid) {
+    if (WALLS && !(A.pl.pm & 1u) && a.out_face >= 0 && outflow_plane_index(a.out_face, 0, x, y, z, a) >= 0) return;
+    if (WALLS && (A.pl.pm & 1u)) {      // a solid node holds no fluid
 #pragma unroll
       for (int e = 0; e < NE; ++e) sum[e] = T(0);
       vst<T, NE>(at(gptr<T>(a.conc), node * NE), sum);
@@ -583,10 +623,28 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
     zero_acc(mid);
     zero_acc(hi);
     const int p_first = D3 ? z0 - 1 : 0, p_last = D3 ? z1 : 0;
+    // (a plane ahead: the stored masks' latency then passes under a plane)
+    Pulls ahead = pull_masks(z0 + 1);
+    if (D3) hi.pl = pull_masks(z0);
+    else mid.pl = pull_masks(0);
+    // With walls and f as populations (no occupancy to lose: the update holds
+    // fewer waves) the next plane is fetched while the current one is
+    // processed, which a small lattice's few workgroups need.
+    constexpr bool AHEAD = D3 && WALLS && !FR && AOS;
+    Fill nxt[2];
+    bool coming = false;
+    if constexpr (AHEAD) coming = fetch_plane(p_first, nxt);
     for (int p = p_first; p <= p_last; ++p) {
       if (p != p_first) __syncthreads();      // every read of the previous plane is done
-      const bool have = load_plane(p);
-      __syncthreads();
+      bool have = coming;
+      if constexpr (AHEAD) {
+        if (have) put_plane(nxt);
+        __syncthreads();
+        if (p < p_last) coming = fetch_plane(p + 1, nxt);
+      } else {
+        have = load_plane(p);
+        __syncthreads();
+      }
       if (active) {
         plane_step(p, have, lo, mid, hi, WF);
         if (!D3) finish(mid, 0);
@@ -595,6 +653,10 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
       lo = mid;
       mid = hi;
       zero_acc(hi);
+      if (D3) {
+        hi.pl = ahead;
+        ahead = pull_masks(p + 3);
+      }
     }
   };
   if (flocal) march(std::false_type{});
@@ -822,7 +884,7 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
   // values, beyond the outflow face the convected ghost values.
   T nxt[2][NEP + 1];
   bool nok[2];
-  auto fetch_plane = [&](int gz) {
+  auto fetch_into = [&](int gz, T (&nxt)[2][NEP + 1], bool (&nok)[2]) {
     int plane_face = -1;
     bool skip = false;
     if (gz < 0 || gz >= a.nz) {
@@ -862,7 +924,7 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
       nxt[r][NEP] = *at(eb, node);
     }
   };
-  auto put_plane = [&](int slot) {
+  auto put_from = [&](int slot, const T (&nxt)[2][NEP + 1], const bool (&nok)[2]) {
     T* base = sm + slot * plane_stride;
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
@@ -872,6 +934,8 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
       base[EOFF + idx] = nxt[r][NEP];
     }
   };
+  auto fetch_plane = [&](int gz) { fetch_into(gz, nxt, nok); };
+  auto put_plane = [&](int slot) { put_from(slot, nxt, nok); };
   auto load_plane = [&](int slot, int gz) {
     fetch_plane(gz);
     put_plane(slot);
@@ -883,7 +947,8 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
   T f[Q];
   constexpr T FSC = static_cast<T>(S::scale);
   constexpr T FINV = T(1) / FSC;
-  auto load_f = [&](int z) {
+  // pm: the node's pull mask, wl: its links into walls (of pm)
+  auto load_f = [&](int z, uint32_t pm, uint32_t wl) {
     if constexpr (WALLS) {
       // convective outflow: plane N's post-streaming f is in the plane buffer
       const int op = a.out_face >= 0 ? outflow_plane_index(a.out_face, 0, x, y, z, a) : -1;
@@ -899,23 +964,35 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
       const uint32_t node = uint32_t(x) + nx * uint32_t(y) + nxy * uint32_t(z);
       const Nbr nb = neighbours<L, WALLS>(x, y, z, a);
       const size_t fst = fresh(size_t(a.fstride));
+      // bounced back at a wall: this node's own opposite population, by its
+      // address rather than in a branch per direction
 #pragma unroll
       for (int k = 1; k < Q; ++k) {
-        if (pulled_from_wall<L, WALLS>(nb, k)) {
-          f[k] = S::ld_raw(at(fsrc + size_t(opposite(k) - 1) * fst, node), 0);
-          // open face: velocity Dirichlet, bounce-back plus 2 w_k (e_k . v_b) / c_s^2
-          const int fc = entry_face<L, WALLS>(nb, k, open);
-          if (fc >= 0) f[k] += FB->fcorr[fc][k] * FSC;
-        } else {
-          f[k] = S::ld_raw(at(fsrc + size_t(k - 1) * fst, upstream<L>(nb, k)), 0);
+        const FS* src = at(fsrc + size_t(k - 1) * fst, upstream<L>(nb, k));
+        if (WALLS && (pm >> k & 1u)) src = at(fsrc + size_t(opposite(k) - 1) * fst, node);
+        f[k] = S::ld_raw(src, 0);
+      }
+      if constexpr (WALLS) {
+        // open face: velocity Dirichlet, bounce-back plus 2 w_k (e_k . v_b) / c_s^2
+        const uint32_t om = pm & ~wl;
+        if (om >> 1) {
+#pragma unroll
+          for (int k = 1; k < Q; ++k)
+            if (om >> k & 1u) f[k] += FB->fcorr[open_entry<L>(a, open, x, y, z, k)][k] * FSC;
         }
       }
     }
   };
 
+  Pulls pm_xy{0u, 0u};
+  if constexpr (WALLS) pm_xy = column_pulls<L>(a, open, x, y);
+  auto pull_masks = [&](int z) -> Pulls {
+    if (!WALLS || !active || z >= z1) return {0u, 0u};
+    return node_pulls<L>(a, open, pm_xy, x, y, z);
+  };
   // PL (std::true_type): the run has no stabilising term, the conservative
   // force and hydrodynamics, so those flags are not tested per node
-  auto process = [&](int z, int s_dn, int s_c, int s_up, auto PL) {
+  auto process = [&](int z, int s_dn, int s_c, int s_up, Pulls pulls, auto PL) {
     constexpr bool PLAIN = decltype(PL)::value;
     const bool omega = !PLAIN && (a.flags & kFlagOmega);
     const bool potential = !PLAIN && (a.flags & kFlagPotential);
@@ -923,16 +1000,7 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
     // immediate offsets from one base instead of hoisted per-entry addresses
     const NFLBM_CONST DevParams<T>& P = *fresh_const(P0);
     const int li = (ty + 1) * PX + (tx + 1);
-    // solid geometry: this node's pull mask (bit k: the neighbour x - e_k is
-    // solid or beyond a wall face; bit 0: this node is solid)
-    bool geom = false;
-    uint32_t pm = 0u;
-    if constexpr (WALLS) {
-      if (a.bb) {
-        geom = true;
-        pm = a.bb[uint32_t(x) + nx * uint32_t(y) + nxy * uint32_t(z)];
-      }
-    }
+    const uint32_t pm = pulls.pm, wl = pulls.wl;
     // record form of f in a step: the moments of the streamed f are read
     // here, so that the load's latency passes under the stencil (four
     // registers, where the gathered populations would hold eighteen)
@@ -989,13 +1057,10 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
     // A node next to a wall face goes direction by direction; every other
     // node, in every kernel variant and tile shape alike, goes by pairs, so a
     // node's result depends only on its position.
-    bool near_wall = false;
-    if constexpr (WALLS) {
-      near_wall = geom ? (pm >> 1) != 0u
-                       : (a.wall_x && ((x == 0 && plain(0)) || (x == a.nx - 1 && plain(1)))) ||
-                             (a.wall_y && ((y == 0 && plain(2)) || (y == a.ny - 1 && plain(3)))) ||
-                             (a.wall_z && ((z == 0 && plain(4)) || (z == a.nz - 1 && plain(5))));
-    }
+    const bool near_wall = WALLS && (a.bb ? pm : wl) >> 1;
+    auto fp64_fence = [] {         // as in the reconstruction
+      if constexpr (D3 && sizeof(T) == 8) __builtin_amdgcn_sched_barrier(0);
+    };
     if (!near_wall) {
       // over the opposite pairs {k, k+1}, with psi+ = psi(x + e_k) and
       // psi- = psi(x - e_k) the gradient takes w_k e_k (psi+ - psi-) and the
@@ -1017,6 +1082,7 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
           if (ey != 0) gC[i][1] = fma((ey > 0) ? wk : -wk, dd, gC[i][1]);
           if (ez != 0) gC[i][2] = fma((ez > 0) ? wk : -wk, dd, gC[i][2]);
         }
+        fp64_fence();
         const T dE = *nbr_e(ex, ey, ez) - *nbr_e(-ex, -ey, -ez);
         if (ex != 0) gE[0] = fma((ex > 0) ? wk : -wk, dE, gE[0]);
         if (ey != 0) gE[1] = fma((ey > 0) ? wk : -wk, dE, gE[1]);
@@ -1027,41 +1093,27 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
       for (int i = 0; i < NE; ++i) lap[i] = fma(-wsum, c[i], lap[i]);
     } else {
       // next to a wall, direction by direction: a neighbour inside a wall
-      // takes the centre value, i.e. contributes nothing
-      Nbr nbw;
-      if (geom && open) nbw = neighbours<L, WALLS>(x, y, z, a);
+      // takes the centre value, i.e. contributes nothing.  The centre is read
+      // in its place: a difference of 0, and no branch per direction.
 #pragma unroll
       for (int k = 1; k < Q; ++k) {
         const int ex = L::e[k][0], ey = L::e[k][1], ez = L::e[k][2];
         const T wk = static_cast<T>(L::w[k]);
-        bool wall = false;
-        if (geom) {
-          wall = (pm >> opposite(k)) & 1u;      // x + e_k is x - e_(opposite k)
-          // beyond an open face (not continuing a solid node): an ordinary
-          // LDS position holding the face's values
-          if (wall && open && entry_face<L, WALLS>(nbw, opposite(k), open) >= 0) wall = false;
-        } else {
-          // a neighbour beyond an open face is an ordinary LDS position
-          if (ex != 0 && a.wall_x) wall |= (x + ex < 0 && plain(0)) || (x + ex >= a.nx && plain(1));
-          if (ey != 0 && a.wall_y) wall |= (y + ey < 0 && plain(2)) || (y + ey >= a.ny && plain(3));
-          if (ez != 0 && a.wall_z) wall |= (z + ez < 0 && plain(4)) || (z + ez >= a.nz && plain(5));
-        }
-        if (!wall) {
-          T rn[NEP];
-          read_c(nbr(ex, ey, ez), rn);
+        const bool wall = wl >> opposite(k) & 1u;      // x + e_k is x - e_(opposite k)
+        T rn[NEP];
+        read_c(wall ? nbr(0, 0, 0) : nbr(ex, ey, ez), rn);
 #pragma unroll
-          for (int i = 0; i < NE; ++i) {
-            const T d = rn[i] - c[i];
-            lap[i] = fma(wk, d, lap[i]);
-            if (ex != 0) gC[i][0] = fma((ex > 0) ? wk : -wk, d, gC[i][0]);
-            if (ey != 0) gC[i][1] = fma((ey > 0) ? wk : -wk, d, gC[i][1]);
-            if (ez != 0) gC[i][2] = fma((ez > 0) ? wk : -wk, d, gC[i][2]);
-          }
-          const T dE = *nbr_e(ex, ey, ez) - E0;
-          if (ex != 0) gE[0] = fma((ex > 0) ? wk : -wk, dE, gE[0]);
-          if (ey != 0) gE[1] = fma((ey > 0) ? wk : -wk, dE, gE[1]);
-          if (ez != 0) gE[2] = fma((ez > 0) ? wk : -wk, dE, gE[2]);
+        for (int i = 0; i < NE; ++i) {
+          const T d = rn[i] - c[i];
+          lap[i] = fma(wk, d, lap[i]);
+          if (ex != 0) gC[i][0] = fma((ex > 0) ? wk : -wk, d, gC[i][0]);
+          if (ey != 0) gC[i][1] = fma((ey > 0) ? wk : -wk, d, gC[i][1]);
+          if (ez != 0) gC[i][2] = fma((ez > 0) ? wk : -wk, d, gC[i][2]);
         }
+        const T dE = *(wall ? nbr_e(0, 0, 0) : nbr_e(ex, ey, ez)) - E0;
+        if (ex != 0) gE[0] = fma((ex > 0) ? wk : -wk, dE, gE[0]);
+        if (ey != 0) gE[1] = fma((ey > 0) ? wk : -wk, dE, gE[1]);
+        if (ez != 0) gE[2] = fma((ez > 0) ? wk : -wk, dE, gE[2]);
       }
     }
     // the implicit component is 1 - sum of the others, so each of its stencil
@@ -1201,7 +1253,7 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
 #pragma unroll
       for (int d = 0; d < 3; ++d) v[d] = fma(T(0.5), F[d], fm[1 + d]);
     } else if (hydro && GM != 2) {
-      load_f(z);
+      load_f(z, pm, wl);
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
         const int k = 2 * p + 1;
@@ -1425,9 +1477,24 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
       // values fetched into registers while the current plane is processed
       // and written to LDS at the top of the next iteration, so that the
       // fill's load latency overlaps the compute.
-      load_plane(0, z0 - 1);
-      load_plane(1, z0);
-      fetch_plane(z0 + 1);
+      // With walls the first three planes are fetched together: on a small lattice a run
+      // is one plane, and their latencies one after the other were a third of
+      // the kernel (16 x 16 x 192, N = 6, walls on z: 14.6 -> 12.1 us with
+      // the pull masks, a single plane's run).
+      if constexpr (WALLS) {
+        T dn[2][NEP + 1], c0[2][NEP + 1];
+        bool dok[2], cok[2];
+        fetch_into(z0 - 1, dn, dok);
+        fetch_into(z0, c0, cok);
+        fetch_plane(z0 + 1);
+        put_from(0, dn, dok);
+        put_from(1, c0, cok);
+      } else {
+        load_plane(0, z0 - 1);
+        load_plane(1, z0);
+        fetch_plane(z0 + 1);
+      }
+      Pulls next = pull_masks(z0);
       for (int z = z0; z < z1; ++z) {
         const int r = z - z0;
         const int s_dn = r % 3, s_c = (r + 1) % 3, s_up = (r + 2) % 3;
@@ -1435,7 +1502,9 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
         put_plane(s_up);
         __syncthreads();
         if (z + 1 < z1) fetch_plane(z + 2);
-        if (active) process(z, s_dn, s_c, s_up, PL);
+        const Pulls now = next;
+        next = pull_masks(z + 1);
+        if (active) process(z, s_dn, s_c, s_up, now, PL);
         __syncthreads();
       }
     } else if constexpr (D3) {
@@ -1450,13 +1519,13 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
         asm volatile("" ::: "memory");
         load_plane(s_up, z + 1);
         __syncthreads();
-        if (active) process(z, s_dn, s_c, s_up, PL);
+        if (active) process(z, s_dn, s_c, s_up, pull_masks(z), PL);
         __syncthreads();
       }
     } else {
       load_plane(0, 0);
       __syncthreads();
-      if (active) process(0, 0, 0, 0, PL);
+      if (active) process(0, 0, 0, 0, pull_masks(0), PL);
     }
   };
   if constexpr (MODE == kModeStep) {
@@ -1730,6 +1799,22 @@ __global__ void __launch_bounds__(256) k_build_bb(const unsigned char* __restric
     if (blocked) m |= 1u << k;
   }
   bb[node] = m;
+}
+
+// The directions whose populations enter each node across an open face.
+template <class L>
+__global__ void __launch_bounds__(256) k_build_ob(int open, uint32_t* __restrict__ ob, StepArgs a) {
+  const size_t node = size_t(blockIdx.x) * 256 + threadIdx.x;
+  if (node >= static_cast<size_t>(a.n)) return;
+  const int x = int(node % size_t(a.nx));
+  const int y = int((node / size_t(a.nx)) % size_t(a.ny));
+  const int z = int(node / (size_t(a.nx) * size_t(a.ny)));
+  const Nbr nb = neighbours<L, true>(x, y, z, a);
+  uint32_t m = 0u;
+#pragma unroll
+  for (int k = 1; k < L::Q; ++k)
+    if (pulled_from_wall<L, true>(nb, k) && entry_face<L, true>(nb, k, open) >= 0) m |= 1u << k;
+  ob[node] = m;
 }
 
 // ------------------------------------------------------------ domain size
@@ -2203,6 +2288,13 @@ hipError_t launch_conc(int lat, int nc, int store, const StepArgs& a, hipStream_
 hipError_t launch_batch_step(int lat, int nc, int store, const BatchLaunch& b, hipStream_t s) {
   const KernelSet& k = kset(store, lat, nc);
   return k.batch ? k.batch(b, s) : hipErrorInvalidValue;
+}
+
+hipError_t launch_build_ob(int lat, int open, uint32_t* ob, const StepArgs& a, hipStream_t s) {
+  const unsigned blocks = static_cast<unsigned>((a.n + 255) / 256);
+  if (lat == 0) hipLaunchKernelGGL(k_build_ob<D2Q9>, dim3(blocks), dim3(256), 0, s, open, ob, a);
+  else hipLaunchKernelGGL(k_build_ob<D3Q19>, dim3(blocks), dim3(256), 0, s, open, ob, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_build_bb(int lat, const unsigned char* solid, uint32_t* bb, const StepArgs& a,
