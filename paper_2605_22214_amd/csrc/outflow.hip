@@ -181,6 +181,70 @@ __device__ __forceinline__ void pull_g_all(const StepArgs& a, const Nbr& nb, uin
   for (int e = 0; e < NE; ++e) q[e] = S::unpack(r[e]);
 }
 
+// Both, from one set of loads, where g and f are node records and this is not
+// the first step: the source's record without a branch (a population bounced
+// back at a wall is the node's own opposite one, the record's with v and F
+// negated), so that a wavefront's directions are all in flight before the
+// first is used.  One at a time, each behind the last one's branches, they
+// were most of the outflow's time (see k_outflow_apply).
+template <class L, int NE, int ST>
+struct RecordPull {
+  using S = StoreT<ST>;
+  using T = typename S::T;
+  T c[NE], mu[NE], v4[4], fr[4];
+  bool wall;
+  __device__ __forceinline__ void load(const StepArgs& a, const Nbr& nb, uint32_t node, int k, bool with_g) {
+    wall = k > 0 && pulled_from_wall<L, true>(nb, k);
+    const uint32_t src = (k == 0 || wall) ? node : upstream<L>(nb, k);
+    rec_load<S, 4>(a.vel, src * 4u, v4, T(S::vel_scale));
+    if (k > 0) rec_load<S, 4>(a.frec, src * 4u, fr, T(S::vel_scale));
+    if (with_g) {
+      vld<T, NE>(gptr<const T>(a.cprev) + size_t(src) * NE, c);
+      rec_load<S, NE>(a.mu, src * uint32_t(NE), mu, T(S::mu_scale));
+    }
+  }
+  // s_k / w_k and f_k / w_k (k > 0)
+  __device__ __forceinline__ T s_over_w(int k, T& ev) const {
+    const T v[3] = {v4[0], v4[1], v4[2]};
+    ev = proj<L>((k & 1) ? k : k - 1, v);
+    if (wall) ev = -ev;
+    return fma(ev, fma(T(4.5), ev, (k & 1) ? T(3) : -T(3)), v4[3]);
+  }
+  __device__ __forceinline__ T f(int k, const FaceBC<T>* FB, int open, const Nbr& nb) const {
+    T ev;
+    const T u = s_over_w(k, ev);
+    const T F[3] = {fr[1], fr[2], fr[3]};
+    T eF = proj<L>((k & 1) ? k : k - 1, F);
+    if (wall) eF = -eF;
+    T v = static_cast<T>(L::w[k]) * (u + fma(eF, fma(T(4.5), ev, (k & 1) ? T(1.5) : -T(1.5)), fr[0]));
+    if (wall && open) {
+      const int fc = entry_face<L, true>(nb, k, open);
+      if (fc >= 0) v += FB->fcorr[fc][k];
+    }
+    return v;
+  }
+  __device__ __forceinline__ void g(int k, T m, const FaceBC<T>* FB, int open, const Nbr& nb, T (&q)[NE]) const {
+    if (k == 0) {
+      const T s0 = static_cast<T>(L::w[0]) * v4[3];
+#pragma unroll
+      for (int e = 0; e < NE; ++e) q[e] = c[e] + fma(c[e], s0, (static_cast<T>(1.0 - L::w[0]) * m) * mu[e]);
+      return;
+    }
+    T ev;
+    const T u = s_over_w(k, ev);
+    const T wk = static_cast<T>(L::w[k]);
+#pragma unroll
+    for (int e = 0; e < NE; ++e) q[e] = fma(c[e], wk * u, -(wk * m) * mu[e]);
+    if (wall && open) {
+      const int fc = entry_face<L, true>(nb, k, open);
+      if (fc >= 0) {
+#pragma unroll
+        for (int e = 0; e < NE; ++e) q[e] = FB->gsum[fc][e][k] - q[e];
+      }
+    }
+  }
+};
+
 }  // namespace
 
 // Work split of both kernels: a workgroup takes kOutNodes plane nodes (one
@@ -189,6 +253,8 @@ __device__ __forceinline__ void pull_g_all(const StepArgs& a, const Nbr& nb, uin
 // sums its directions in that order; the workgroup then adds the waves'
 // partial sums in wave order, so every result has one fixed order.
 constexpr int kOutWaves = kOutThreads / kOutNodes;
+template <class L>
+constexpr int kOutDirs = (L::Q + kOutWaves - 1) / kOutWaves;   // directions a wavefront takes, at most
 
 // Runs f(std::integral_constant<int, w>) for the wave index w of this thread,
 // so that a wave's direction loop has compile-time directions.
@@ -226,7 +292,27 @@ __global__ void __launch_bounds__(kOutThreads) k_outflow_mom(OutflowArgs o) {
     const uint32_t node = uint32_t(x) + uint32_t(a.nx) * (uint32_t(y) + uint32_t(a.ny) * uint32_t(z));
     const FaceBC<T>* FB = gptr<const FaceBC<T>>(a.faces);
     const int open = FB ? FB->open : 0;
-    if (!solid_node<true>(nb)) {       // solid nodes hold no fluid
+    const bool records = (a.flags & kFlagFRecord) && !(a.flags & kFlagFLocal);
+    if (records && !solid_node<true>(nb)) {
+      for_wave(wave, [&](auto WC) {
+        constexpr int W = decltype(WC)::value;
+        RecordPull<L, NC - 1, ST> r[kOutDirs<L>];
+#pragma unroll
+        for (int j = 0; j < kOutDirs<L>; ++j) {
+          const int k = W + j * kOutWaves;
+          if (k > 0 && k < L::Q && L::e[k][ax] != 0) r[j].load(a, nb, node, k, false);
+        }
+#pragma unroll
+        for (int j = 0; j < kOutDirs<L>; ++j) {
+          const int k = W + j * kOutWaves;
+          if (k > 0 && k < L::Q && L::e[k][ax] != 0) {
+            const double v = static_cast<double>(r[j].f(k, FB, open, nb));
+            mom += (L::e[k][ax] > 0) ? v : -v;
+          }
+        }
+      });
+      mom *= sgn;
+    } else if (!solid_node<true>(nb)) {       // solid nodes hold no fluid
       for_wave(wave, [&](auto WC) {
         constexpr int W = decltype(WC)::value;
 #pragma unroll
@@ -263,6 +349,55 @@ __global__ void __launch_bounds__(kOutThreads) k_outflow_apply(OutflowArgs o) {
   const int tid = static_cast<int>(threadIdx.x);
   const int lane = tid % kOutNodes;
   const int wave = tid / kOutNodes;
+  const int p = static_cast<int>(blockIdx.x) * kOutNodes + lane;
+  const bool active = p < PL;
+  const size_t P = static_cast<size_t>(PL);
+  T* of = gptr<T>(a.out_f);
+  T* og = gptr<T>(a.out_g);
+  T* gh = gptr<T>(a.out_ghost);
+  // plane N's node (the boundary plane) and, for convecting, plane N-1's
+  int xN = 0, yN = 0, zN = 0;
+  if (active) plane_node(ax, plane_pos(face, 0, a), p, a, xN, yN, zN);
+  const uint32_t nodeN = uint32_t(xN) + uint32_t(a.nx) * (uint32_t(yN) + uint32_t(a.ny) * uint32_t(zN));
+  bool solid = false;
+  if (active) solid = solid_node<true>(neighbours<L, true>(xN, yN, zN, a));
+  const bool moments = (a.flags & kFlagMoments) != 0;
+  if (o.start == 2 && !moments) return;          // nothing to refresh
+  // node records: the pulled populations and the buffers' values of this
+  // wave's directions, all in flight while U is summed (N = 4, FP32, a
+  // 128 x 128 x face)
+  const bool records = o.start == 0 && (a.flags & kFlagFRecord) && !(a.flags & kFlagFLocal);
+  constexpr int ND = kOutDirs<L>;
+  T qf[ND], sf[ND], qg[ND][NE], sg[ND][NE];
+  if (records && active && !solid) {
+    int x, y, z;
+    plane_node(ax, plane_pos(face, 1, a), p, a, x, y, z);
+    const Nbr nb = neighbours<L, true>(x, y, z, a);
+    const uint32_t node = uint32_t(x) + uint32_t(a.nx) * (uint32_t(y) + uint32_t(a.ny) * uint32_t(z));
+    const FaceBC<T>* FB = gptr<const FaceBC<T>>(a.faces);
+    const int open = FB ? FB->open : 0;
+    const T pm = gptr<const DevParams<T>>(a.params)->m;
+    for_wave(wave, [&](auto WC) {
+      constexpr int W = decltype(WC)::value;
+      RecordPull<L, NE, ST> r[ND];
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        const int k = W + j * kOutWaves;
+        if (k >= Q) continue;
+        r[j].load(a, nb, node, k, true);
+        if (k > 0) sf[j] = of[size_t(k - 1) * P + p];
+#pragma unroll
+        for (int e = 0; e < NE; ++e) sg[j][e] = og[(size_t(e) * Q + k) * P + p];
+      }
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        const int k = W + j * kOutWaves;
+        if (k >= Q) continue;
+        if (k > 0) qf[j] = r[j].f(k, FB, open, nb);
+        r[j].g(k, pm, FB, open, nb, qg[j]);
+      }
+    });
+  }
   // U from the partial sums, in the same order in every workgroup
   double U = 0.0;
   if (o.start == 0) {
@@ -278,20 +413,6 @@ __global__ void __launch_bounds__(kOutThreads) k_outflow_apply(OutflowArgs o) {
     if (!(U > 0.0)) U = 0.0;
     if (blockIdx.x == 0 && tid == 0) o.u[0] = U;
   }
-  const int p = static_cast<int>(blockIdx.x) * kOutNodes + lane;
-  const bool active = p < PL;
-  const size_t P = static_cast<size_t>(PL);
-  T* of = gptr<T>(a.out_f);
-  T* og = gptr<T>(a.out_g);
-  T* gh = gptr<T>(a.out_ghost);
-  // plane N's node (the boundary plane) and, for convecting, plane N-1's
-  int xN = 0, yN = 0, zN = 0;
-  if (active) plane_node(ax, plane_pos(face, 0, a), p, a, xN, yN, zN);
-  const uint32_t nodeN = uint32_t(xN) + uint32_t(a.nx) * (uint32_t(yN) + uint32_t(a.ny) * uint32_t(zN));
-  bool solid = false;
-  if (active) solid = solid_node<true>(neighbours<L, true>(xN, yN, zN, a));
-  const bool moments = (a.flags & kFlagMoments) != 0;
-  if (o.start == 2 && !moments) return;          // nothing to refresh
   // this wave's directions: blend (start 0), capture (start 1) or only read
   // back (start 2) their plane-N values, and sum them per node
   T m[NE], r[NE], fm[4];
@@ -299,7 +420,33 @@ __global__ void __launch_bounds__(kOutThreads) k_outflow_apply(OutflowArgs o) {
   for (int e = 0; e < NE; ++e) m[e] = r[e] = T(0);
 #pragma unroll
   for (int d = 0; d < 4; ++d) fm[d] = T(0);
-  if (active && !solid) {
+  if (records && active && !solid) {
+    const T u = static_cast<T>(U);
+    const T den = T(1) + u;
+    for_wave(wave, [&](auto WC) {
+      constexpr int W = decltype(WC)::value;
+#pragma unroll
+      for (int j = 0; j < ND; ++j) {
+        const int k = W + j * kOutWaves;
+        if (k >= Q) continue;
+        if (k > 0) {
+          const T v = (sf[j] + u * qf[j]) / den;
+          of[size_t(k - 1) * P + p] = v;
+          fm[0] += v;
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            if (L::e[k][d] != 0) fm[1 + d] += (L::e[k][d] > 0) ? v : -v;
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          const T v = (sg[j][e] + u * qg[j][e]) / den;
+          og[(size_t(e) * Q + k) * P + p] = v;
+          if (k == 0) r[e] = v;
+          else m[e] += v;
+        }
+      }
+    });
+  } else if (active && !solid) {
     int x, y, z;
     plane_node(ax, plane_pos(face, o.start == 0 ? 1 : 0, a), p, a, x, y, z);
     const Nbr nb = neighbours<L, true>(x, y, z, a);
