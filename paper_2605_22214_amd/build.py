@@ -58,8 +58,8 @@ UNITS = [
     ("coeffs.cpp", "coeffs.o", False, []),
     ("api.cpp", "api.o", False, []),
 ] + _kernel_units() + [
-    ("fused2d.hip", f"fused2d_{name}.o", True, [f"-DNFLBM_UNIT_STORE={st}"])
-    for st, name in ((0, "f64"), (1, "f32"), (2, "f16s"))
+    (f"{src}.hip", f"{src}_{name}.o", True, [f"-DNFLBM_UNIT_STORE={st}"])
+    for src in ("fused2d", "fused_mob") for st, name in ((0, "f64"), (1, "f32"), (2, "f16s"))
 ] + [
     ("kernels.hip", "kernels_common.o", True, ["-DNFLBM_UNIT_STORE=-1"]),
     ("mobility.hip", "mobility.o", True, []),

@@ -698,6 +698,69 @@ int fused_count(long long n, long long launches, long long i) {
   return static_cast<int>(n / launches + (i < n % launches ? 1 : 0));
 }
 
+// Checks of the next n steps for non-finite values, as a bit each.
+uint32_t nan_mask(nflbm_sim* s, int n) {
+  uint32_t mask = 0;
+  for (int t = 0; t < n; ++t) {
+    ++s->step_count;
+    if (s->nan_every > 0 && s->step_count % s->nan_every == 0) mask |= 1u << t;
+  }
+  return mask;
+}
+
+// Fused steps of the concentration-dependent mobility (fused_mob.hip): a
+// periodic D2Q9 lattice, diffusive-only and every tau_g = 1, where the
+// collision leaves the source terms alone.
+bool fused_mob_now(const nflbm_sim* s) {
+  return s->lat == NFLBM_D2Q9 && s->c2c2 && (s->step_flags & kFlagNoHydro) && !(s->step_flags & kFlagNeedG) &&
+         !s->wall[0] && !s->wall[1] && !s->bb;
+}
+
+// Two steps a launch where LDS holds their tiles, which halves what a launch
+// costs for a halo of five nodes instead of two.
+bool fused_mob_plan(const nflbm_sim* s, FusedPlan* p, size_t* lds) {
+  const FusedPlan plans[] = {{5, 2, 14, 512}, {5, 1, 16, 512}, {5, 1, 8, 512}, {5, 1, 4, 512}};
+  for (const FusedPlan& q : plans) {
+    *lds = fused_mob_position_bytes(s->N, s->ts) * 32 * size_t(q.h + 2 * (3 * q.T - 1));
+    if (*lds > s->lds_max) continue;
+    *p = q;
+    return true;
+  }
+  return false;
+}
+
+int run_mob_steps(nflbm_sim* s, long long n, const FusedPlan& p, size_t lds, bool* checked) {
+  FusedMobArgs a{};
+  a.params = s->params;
+  a.mob = s->mob;
+  a.nanflag = s->nanflag;
+  a.gstride = static_cast<long long>(s->gstride);
+  a.nx = s->nx;
+  a.ny = s->ny;
+  const int wmax = 32 - 2 * (3 * p.T - 1);
+  a.tiles_x = (s->nx + wmax - 1) / wmax;
+  a.tile_w = (s->nx + a.tiles_x - 1) / a.tiles_x;
+  int ty = (s->ny + p.h - 1) / p.h;
+  a.tile_h = (s->ny + ty - 1) / ty;
+  ty = (s->ny + a.tile_h - 1) / a.tile_h;
+  a.flags = s->step_flags;
+  while (n > 0) {
+    const int k = static_cast<int>(std::min<long long>(n, p.T));
+    a.gk_src = s->gk[s->cur];
+    a.g0_src = s->g0[s->cur];
+    a.gk_dst = s->gk[s->cur ^ 1];
+    a.g0_dst = s->g0[s->cur ^ 1];
+    const uint32_t mask = nan_mask(s, k);
+    if (mask) *checked = true;
+    const auto launch = s->store == NFLBM_FP64 ? launch_fused_mob_0
+                                               : s->store == NFLBM_FP32 ? launch_fused_mob_1 : launch_fused_mob_2;
+    HIPCHK(s, launch(s->N, a, a.tiles_x * ty, k, mask, lds, s->stream));
+    s->cur ^= 1;
+    n -= k;
+  }
+  return NFLBM_OK;
+}
+
 // n steps of s on its stream; *checked is set when one of them checked for
 // non-finite values.
 int run_steps(nflbm_sim* s, long long n, bool* checked) {
@@ -706,6 +769,8 @@ int run_steps(nflbm_sim* s, long long n, bool* checked) {
     if (rc != NFLBM_OK) return rc;
   }
   FusedPlan p;
+  size_t lds = 0;
+  if (n >= 2 && fused_mob_now(s) && fused_mob_plan(s, &p, &lds)) return run_mob_steps(s, n, p, lds, checked);
   if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p)) {
     if (fused_launches(n, p.T) > n) {      // one step a launch, an odd number
       const int rc = launch_step(s, nullptr, nullptr, checked);
@@ -724,11 +789,7 @@ int run_steps(nflbm_sim* s, long long n, bool* checked) {
     for (long long i = 0; i < launches; ++i) {
       f.one = &a[i & 1];
       f.nsteps = fused_count(n, launches, i);
-      f.nanmask = 0;
-      for (int t = 0; t < f.nsteps; ++t) {
-        ++s->step_count;
-        if (s->nan_every > 0 && s->step_count % s->nan_every == 0) f.nanmask |= 1u << t;
-      }
+      f.nanmask = nan_mask(s, f.nsteps);
       if (f.nanmask) *checked = true;
       HIPCHK(s, launch_fused(s, f, s->stream));
     }

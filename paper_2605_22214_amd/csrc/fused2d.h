@@ -42,6 +42,30 @@ inline size_t fused_position_bytes(int nc, size_t ts, bool frecord) {
   return (3 * size_t(nc - 1) + (frecord ? 10 : 0)) * ts;
 }
 
+// One simulation with the concentration-dependent mobility (fused_mob.hip):
+// the populations before and after the launch.
+struct FusedMobArgs {
+  const void* gk_src;
+  const void* g0_src;
+  void* gk_dst;
+  void* g0_dst;
+  const void* params;         // DevParams<T>
+  const void* mob;            // MobParams<T>
+  int* nanflag;
+  long long gstride;
+  int nx, ny;
+  int tile_w, tile_h, tiles_x;
+  int flags;
+};
+// LDS bytes of one position.
+inline size_t fused_mob_position_bytes(int nc, size_t ts) { return (2 * size_t(nc) + 3 * size_t(nc - 1)) * ts; }
+
+hipError_t launch_fused_mob_0(int nc, const FusedMobArgs& a, int blocks, int nsteps, uint32_t nanmask, size_t lds,
+                              hipStream_t s);
+hipError_t launch_fused_mob_1(int nc, const FusedMobArgs& a, int blocks, int nsteps, uint32_t nanmask, size_t lds,
+                              hipStream_t s);
+hipError_t launch_fused_mob_2(int nc, const FusedMobArgs& a, int blocks, int nsteps, uint32_t nanmask, size_t lds,
+                              hipStream_t s);
 hipError_t launch_fused2d_0(int nc, const FusedLaunch& f, hipStream_t s);
 hipError_t launch_fused2d_1(int nc, const FusedLaunch& f, hipStream_t s);
 hipError_t launch_fused2d_2(int nc, const FusedLaunch& f, hipStream_t s);

@@ -92,3 +92,43 @@ def test_fused_steps_report_nan():
     s.step(4)                # the fifth is
     with pytest.raises(nf.NflbmError):
         s.synchronize()
+
+
+MOB_CASES = [
+    ((90, 70), 4, "fp32", 0.0),
+    ((5, 3), 3, "fp64", 0.05),       # smaller than the halo
+    ((1, 1), 2, "fp32", 0.0),
+    ((45, 131), 4, "fp16s", 0.05),
+    ((67, 50), 8, "fp64", 0.0),      # the largest LDS records: one step a launch
+    ((60, 47), 6, "fp32", 0.05),
+]
+
+
+@pytest.mark.parametrize("shape,N,precision,omega", MOB_CASES)
+def test_fused_mobility_equals_single_steps(shape, N, precision, omega):
+    cfg = _config(shape, N, precision, nf.FLAG_NO_HYDRO | nf.FLAG_C2C2_MOBILITY, omega)
+    cfg["m"] = 10.0
+    a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+    C = _noise(shape, N, 3)
+    a.set_fields(C)
+    b.set_fields(C)
+    for _ in range(14):
+        a.step(1)
+    b.step(2)
+    b.step(3)
+    b.step(9)
+    if shape != (1, 1):              # a single node stays as it is
+        assert np.abs(a.get_field("C") - C).max() > 1e-6
+    assert np.array_equal(a.get_field("C"), b.get_field("C"))
+    assert np.array_equal(a.get_field("G_RAW"), b.get_field("G_RAW"))
+
+
+def test_fused_mobility_steps_report_nan():
+    cfg = _config((70, 50), 4, "fp32", nf.FLAG_NO_HYDRO | nf.FLAG_C2C2_MOBILITY)
+    s = nf.Simulation(**cfg)
+    C = _noise((70, 50), 4, 2)
+    C[0, 0, 20, 30] = np.nan
+    s.set_fields(C)
+    s.step(16)
+    with pytest.raises(nf.NflbmError):
+        s.synchronize()
