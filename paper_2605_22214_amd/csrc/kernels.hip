@@ -502,10 +502,24 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
     auto fluid = [](const Acc& A) { return !WALLS || __any(!(A.pl.pm & 1u)); };
     const bool need_hi = D3 && have && p + 1 >= z0 && p + 1 < z1 && fluid(hi);
     const bool need_lo = D3 && have && p - 1 >= z0 && p - 1 < z1 && fluid(lo);
-    // Away from walls, the node of plane p + 1 (directions (ex, ey, +1)) and
-    // the node of plane p - 1 (directions (ex, ey, -1)) pull from the same
-    // five positions of plane p: each record is read once for both.
+    // Away from walls, the node of plane p + 1 (directions (ex, ey, +1)), the
+    // node of plane p - 1 (directions (ex, ey, -1)) and the node of plane p
+    // (the in-plane axis directions and its rest population) pull from the
+    // same five positions of plane p: each record is read once for the three,
+    // 9 records a node instead of 14.
     const bool merged = D3 && !WALLS && need_hi && need_lo;
+    // the target's own record: its C and the rest population's change
+    auto rest_term = [&](const T (&cs)[NEP], const T (&ms)[NEP], const T (&v4)[4]) {
+      const T s0 = static_cast<T>(L::w[0]) * v4[3];
+      const T m0 = moving_weight_sum<L, T>() * P.m;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        mid.c[e] = cs[e];
+        const T d0 = fma(cs[e], s0, m0 * ms[e]);
+        if constexpr (CLASS) mid.d0[e] = d0;
+        else mid.s[e] += d0;
+      }
+    };
     auto blocked = [](const Acc& A, int k) { return WALLS && (A.pl.pm >> k & 1u); };
     if (merged) {
 #pragma unroll
@@ -516,6 +530,12 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
           read_rec(src_at(L::e[k][0], L::e[k][1]), R, WF);
           acc_rec(hi, R, k, k, WF, negm, std::false_type{});
           acc_rec(lo, R, km, km, WF, negm, std::false_type{});
+          if (L::e[k][0] == 0 && L::e[k][1] == 0) {
+            rest_term(R.cs, R.ms, R.v4);
+          } else {
+            const int kc = direction_of<L>(L::e[k][0], L::e[k][1], 0);
+            acc_rec(mid, R, kc, kc, WF, negm, std::false_type{});
+          }
           fp64_fence();
         }
     }
@@ -526,25 +546,23 @@ __device__ __forceinline__ void conc_tile_m(const StepArgs& a,
     }
     if (p >= z0 && p < z1 && fluid(mid)) {
       const T* own = src_at(0, 0);
-      {
+      if (!merged) {
         T cs[NEP], ms[NEP], v4[4];
         read_pos(own, cs, ms, v4);
-        const T s0 = static_cast<T>(L::w[0]) * v4[3];
-        const T m0 = moving_weight_sum<L, T>() * P.m;
+        rest_term(cs, ms, v4);
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-          mid.c[e] = cs[e];
-          const T d0 = fma(cs[e], s0, m0 * ms[e]);
-          if constexpr (CLASS) mid.d0[e] = d0;
-          else mid.s[e] += d0;
-        }
+        for (int k = 1; k <= 2 * L::DIM; ++k)
+          if (!WALLS && L::e[k][2] == 0) {
+            add_source(mid, src_at(L::e[k][0], L::e[k][1]), k, k, WF, negm);
+            fp64_fence();
+          }
       }
 #pragma unroll
       for (int k = 1; k < Q; ++k) {
         if (blocked(mid, k)) {
           if (mid.pl.wl >> k & 1u) add_source(mid, own, opposite(k), k, WF, negm);
           else add_open(mid, own, k, open_entry<L>(a, open, x, y, p, k), WF, negm);
-        } else if (L::e[k][2] == 0) {
+        } else if (L::e[k][2] == 0 && (WALLS || k > 2 * L::DIM)) {
           add_source(mid, src_at(L::e[k][0], L::e[k][1]), k, k, WF, negm);
           if (!WALLS) fp64_fence();
         }
@@ -1477,10 +1495,10 @@ __device__ __forceinline__ void update_tile(const StepArgs& a,
       // values fetched into registers while the current plane is processed
       // and written to LDS at the top of the next iteration, so that the
       // fill's load latency overlaps the compute.
-      // With walls the first three planes are fetched together: on a small lattice a run
-      // is one plane, and their latencies one after the other were a third of
-      // the kernel (16 x 16 x 192, N = 6, walls on z: 14.6 -> 12.1 us with
-      // the pull masks, a single plane's run).
+      // With walls the first three planes are fetched together: on a small
+      // lattice a run is one plane, and their latencies came one after the
+      // other (16 x 16 x 192, N = 6, walls on z: 14.6 -> 12.1 us with the pull
+      // masks and the gather of f without branches).
       if constexpr (WALLS) {
         T dn[2][NEP + 1], c0[2][NEP + 1];
         bool dok[2], cok[2];
