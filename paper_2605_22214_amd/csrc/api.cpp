@@ -361,6 +361,25 @@ int zchunk_for(const nflbm_sim* s, int l, long long target) {
   return zc;
 }
 
+// The z run of planes that takes least for `tiles` tiles a plane when the chip
+// holds `resident` workgroups at once: rounds of workgroups times the planes a
+// round loads, two of them beyond its run.  The longer run of two alike.
+int fitted_run(const nflbm_sim* s, long long tiles, long long resident) {
+  long long best = 0;
+  int run = 1;
+  for (int zc = 1; zc <= s->nz; ++zc) {
+    const long long groups = tiles * ((s->nz + zc - 1) / zc);
+    const long long cost = (groups + resident - 1) / resident * (zc + 2);
+    if (zc == 1 || cost <= best) {
+      best = cost;
+      run = zc;
+    }
+  }
+  return run;
+}
+
+StepArgs make_args(const nflbm_sim* s, int src);
+
 // Default shapes.  Update: tiles 64 x 4 (16 x 16 when nx <= 16 or when the
 // wider LDS window does not fit), in 3-D a z run per workgroup that leaves
 // about 8192 workgroups (4096 in the float record form of f, whose update
@@ -396,8 +415,28 @@ int default_launch(nflbm_sim* s) {
   const bool f64 = s->store == NFLBM_FP64;
   const long long tu = f64 ? 1024 : xw ? 2048 : (s->fform ? 4096 : 8192);
   const long long tc = f64 ? 1024 : split ? 2048 : (s->gform ? 1024 : 4096);
-  if (!apply_launch(s, l, zchunk_for(s, l, tu))) return -1;
-  return apply_conc_launch(s, l, zchunk_for(s, l, tc)) ? 0 : -1;
+  int zu = zchunk_for(s, l, tu), zc = zchunk_for(s, l, tc);
+  // Record form of f in D3Q19, other than with walls on x alone (above): runs
+  // that fill the chip's workgroup slots in whole rounds, the slots from the
+  // kernels' occupancy.  The update takes 3 workgroups a CU at N = 5 in FP32:
+  // runs of 86 at 256^3, one round of 768, take 0.279 ms, of 16 0.302 ms, of
+  // 64 (a round and a third) 0.359 ms; 200 x 150 x 130 99 -> 82 us; FP16S at
+  // N = 4, 190 x 161 x 175, 76 -> 70 us.  The reconstruction likewise in FP64
+  // (three a CU: 130^3 142 -> 128 us) and FP16S (five: 94 -> 86 us over
+  // 190 x 161 x 175 with the record sharing); in FP32 memory bounds it and
+  // the 1024 workgroups above stay ahead (256^3: runs of 64 0.320 ms, five a CU 0.353
+  // ms; 200 x 150 x 130 96 against 99 us).
+  if (s->lat == NFLBM_D3Q19 && s->fform && !(s->wall[0] && !s->wall[1] && !s->wall[2])) {
+    StepArgs a = make_args(s, s->cur);
+    a.tx_log2 = l;
+    const long long tiles = 1LL * ((s->nx + (1 << l) - 1) >> l) * ((s->ny + (256 >> l) - 1) / (256 >> l));
+    const int gu = groups_per_cu(s->lat, s->N, s->store, a, true);
+    if (gu > 0) zu = fitted_run(s, tiles, 256LL * gu);
+    const int gc = s->store == NFLBM_FP32 ? 0 : groups_per_cu(s->lat, s->N, s->store, a, false);
+    if (gc > 0) zc = fitted_run(s, tiles, 256LL * gc);
+  }
+  if (!apply_launch(s, l, zu)) return -1;
+  return apply_conc_launch(s, l, zc) ? 0 : -1;
 }
 
 int choose_launch(nflbm_sim* s) {

@@ -228,6 +228,9 @@ hipError_t launch_update(int lat, int nc, int store, const StepArgs& a, bool fie
 hipError_t launch_init(int lat, int nc, int store, const InitArgs& a, hipStream_t s);
 hipError_t launch_batch_step(int lat, int nc, int store, const BatchLaunch& b, hipStream_t s);
 hipError_t launch_expand(int lat, int nc, int store, const StepArgs& a, hipStream_t s);
+// Workgroups of the reconstruction (update: of the update) that the launch of
+// a would keep on one CU at once; 0 where that cannot be told (no GPU).
+int groups_per_cu(int lat, int nc, int store, const StepArgs& a, bool update);
 size_t conc_m_lds_bytes(int lat, int nc, int store, int tx_log2, bool frecord);
 // Record form of f: the post-collision f of every node written out in the
 // population layout (f [k-1][node], direction stride a.fstride, compute

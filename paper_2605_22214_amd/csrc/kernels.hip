@@ -1949,6 +1949,7 @@ struct KernelSet {
   hipError_t (*conc)(const StepArgs&, hipStream_t);
   hipError_t (*batch)(const BatchLaunch&, hipStream_t);
   hipError_t (*expand)(const StepArgs&, hipStream_t);
+  int (*groups)(const StepArgs&, bool);
   hipError_t (*expand_f)(const StepArgs&, void*, hipStream_t);
 };
 KernelSet& kernel_set(int store, int lat, int nc);
@@ -1984,6 +1985,35 @@ template <int ST>
 inline int storage_gm(const StepArgs& a) {
   if (!moments(a)) return 0;
   return (a.flags & kFlagFRecord) ? 2 : 1;
+}
+
+// groups_per_cu of the kernel that launch_update_t or launch_conc_t picks for
+// the record form of f (0 for the others: their runs are sized otherwise).
+template <class L, int NC, int ST>
+int groups_t(const StepArgs& a, bool update) {
+  if (storage_gm<ST>(a) != 2) return 0;
+  const int lat = L::DIM == 3 ? 1 : 0;
+  const bool wide = a.tx_log2 == 6;
+  int n = 0;
+  hipError_t e;
+#define GROUPS(K6, K4, LDS)                                                                                  \
+  e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(&K6), 256, LDS)  \
+           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(&K4), 256, LDS);
+#define UPD(W, T) k_update<L, NC, ST, kModeStep, W, T, 2>
+#define CON(W, T) k_conc_m<L, NC - 1, ST, W, T, true>
+  if (update) {
+    const size_t lds = lds_bytes_for<ST>(lat, NC, a.tx_log2);
+    if (any_wall(a)) { GROUPS((UPD(true, 6)), (UPD(true, 4)), lds) } else { GROUPS((UPD(false, 6)), (UPD(false, 4)), lds) }
+  } else {
+    const size_t lds = conc_m_lds_bytes_for<ST>(lat, NC, a.tx_log2, true);
+    if (any_wall(a)) { GROUPS((CON(true, 6)), (CON(true, 4)), lds) } else { GROUPS((CON(false, 6)), (CON(false, 4)), lds) }
+  }
+#undef CON
+#undef UPD
+#undef GROUPS
+  if (e == hipSuccess) return n;
+  (void)hipGetLastError();
+  return 0;
 }
 
 template <class L, int NC, int ST>
@@ -2211,6 +2241,7 @@ void register_nc() {
   k.conc = &launch_conc_t<L, NC, ST>;
   k.batch = &launch_batch_t<L, NC, ST>;
   k.expand = &launch_expand_t<L, NC, ST>;
+  k.groups = &groups_t<L, NC, ST>;
   k.expand_f = &launch_expand_f_t<L, ST>;
 }
 
@@ -2275,6 +2306,11 @@ hipError_t launch_expand_f(int lat, int store, const StepArgs& a, void* out, hip
     if (k.expand_f) return k.expand_f(a, out, s);
   }
   return hipErrorInvalidValue;
+}
+
+int groups_per_cu(int lat, int nc, int store, const StepArgs& a, bool update) {
+  const KernelSet& k = kset(store, lat, nc);
+  return k.groups ? k.groups(a, update) : 0;
 }
 
 hipError_t launch_expand(int lat, int nc, int store, const StepArgs& a, hipStream_t s) {
