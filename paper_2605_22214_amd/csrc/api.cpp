@@ -107,11 +107,6 @@ struct nflbm_sim {
   bool c2c2 = false;
   void* mob = nullptr;
   void* phi = nullptr;
-  // fused D2Q9 steps (fused2d.hip): the other set of node records (v, the f
-  // record, mu~), written by every second launch; the primary arrays hold
-  // the state between calls.  Null where the runs do not qualify or the
-  // memory is not there: the steps are then taken one by one.
-  void* fused_rec = nullptr;
   bool borrowed = false; // state arrays live in caller memory (nflbm_bind_state)
   // domain-size diagnostic: batched R2C plan and its buffers (made on first use)
   hipfftHandle fft = 0;
@@ -126,6 +121,8 @@ struct nflbm_sim {
   unsigned boundary_version = 0;
   void* eb = nullptr;
   void* params = nullptr;
+  // read-back fields [2N+7][n], made on first use; between read-backs the other
+  // record set of the fused steps (fused_args)
   double* fields = nullptr;
   double* red = nullptr;
   // read-back of large fields: pinned slots the device copies into and the
@@ -178,6 +175,7 @@ struct nflbm_batch {
   FusedArgs* fargs = nullptr;
   int2* work_fused = nullptr;
   int blocks_fused = 0;
+  bool fused_wanted = false;   // from the first steps that can be fused on
   std::vector<int> key;     // member parities that args[0..count) was built for
   std::vector<unsigned> versions;   // members' boundary_version at that build
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -265,7 +263,7 @@ void free_device(nflbm_sim* s) {
   s->out_red = nullptr;
   if (s->mob) (void)hipFree(s->mob);
   if (s->phi) (void)hipFree(s->phi);
-  s->mob = s->phi = s->fused_rec = nullptr;   // fused_rec lies in the params block
+  s->mob = s->phi = nullptr;
   if (s->fft_made) (void)hipfftDestroy(s->fft);
   s->fft_made = false;
   if (s->lam) (void)hipFree(s->lam);
@@ -659,6 +657,10 @@ bool fused_plan(const nflbm_sim* const* m, size_t count, FusedPlan* out) {
   const FusedPlan small = wide ? FusedPlan{5, 3, 4, 512} : FusedPlan{5, 4, 4, 1024};
   FusedPlan large = wide ? FusedPlan{5, 2, 16, 512} : FusedPlan{5, 2, 24, 1024};
   if (s->store != NFLBM_FP64 && s->N >= 4) large.threads = 512;
+  // N = 5 and 6 in FP64: all 24 rows in one pass a phase (12 wavefronts), at
+  // 168 VGPRs (28 spilled at N = 6), beat two passes at 204 (nine 300 x 150 lenses,
+  // N = 6: 43.5 -> 38.9 us a step); from N = 7 too many spill
+  if (wide && s->N <= 6) large.threads = 768;
   if (!s->fform) large = FusedPlan{6, 2, 24, 1024};
   const FusedPlan medium{5, 2, 8, 512};
   const FusedPlan plans[] = {small, {5, 3, 8, 512}, medium, large, {5, 2, 16, 512}, medium};
@@ -690,14 +692,37 @@ bool fused_kind(const nflbm_sim* s) {
   return s->lat == NFLBM_D2Q9 && s->gform && (s->fform || (s->step_flags & kFlagNoHydro)) && !s->wall[0] &&
          !s->wall[1];
 }
-bool fused_now(const nflbm_sim* s) { return s->fused_rec && !s->bb && s->out_face < 0 && !s->f_local; }
+bool fused_now(const nflbm_sim* s) { return fused_kind(s) && !s->bb && s->out_face < 0 && !s->f_local; }
+
+
+// Memory for the other record set of the fused steps: the read-back fields'
+// buffer, which a run that is looked at has anyway (a buffer of its own made
+// nflbm_create a third slower).  False where there is none to be had, or none
+// yet while the stream is being captured: the steps are then taken one by one.
+bool fused_memory(nflbm_sim* s, hipStream_t stream) {
+  if (s->fields) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (st != hipStreamCaptureStatusNone) return false;
+  if (hipMalloc(reinterpret_cast<void**>(&s->fields), size_t(2 * s->N + 7) * s->n * sizeof(double)) != hipSuccess) {
+    s->fields = nullptr;
+    (void)hipGetLastError();
+    return false;
+  }
+  return true;
+}
 
 // Arguments of a fused launch from C set `cur`: from the primary records to
-// the others (odd = 0) or back.
+// the others (odd = 0) or back.  The others, (8 + NE) record values a node
+// (v, the f record, mu~), lie in the read-back fields' buffer, whose contents
+// no call leaves behind.
 FusedArgs fused_args(const nflbm_sim* s, const FusedPlan& p, int cur, int odd) {
   FusedArgs a{};
   const size_t n = s->n;
-  unsigned char* o = static_cast<unsigned char*>(s->fused_rec);
+  unsigned char* o = reinterpret_cast<unsigned char*>(s->fields);
   void* rec[2][3] = {{s->mu, s->vel, s->frec}, {o, o, o}};
   if (s->fform) {
     rec[1][0] = o + 8 * n * s->rs;
@@ -810,7 +835,7 @@ int run_steps(nflbm_sim* s, long long n, bool* checked) {
   FusedPlan p;
   size_t lds = 0;
   if (n >= 2 && fused_mob_now(s) && fused_mob_plan(s, &p, &lds)) return run_mob_steps(s, n, p, lds, checked);
-  if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p)) {
+  if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p) && fused_memory(s, s->stream)) {
     if (fused_launches(n, p.T) > n) {      // one step a launch, an odd number
       const int rc = launch_step(s, nullptr, nullptr, checked);
       if (rc != NFLBM_OK) return rc;
@@ -1130,7 +1155,7 @@ void free_batch_tables(nflbm_batch* b) {
 // Whether every member can take fused steps, all in one record form.
 bool fused_batch(const nflbm_batch* b) {
   for (const nflbm_sim* m : b->members)
-    if (!m->fused_rec || m->bb || m->out_face >= 0 || m->fform != b->members[0]->fform) return false;
+    if (!fused_kind(m) || m->bb || m->out_face >= 0 || m->fform != b->members[0]->fform) return false;
   return true;
 }
 
@@ -1184,7 +1209,7 @@ int build_batch_tables(nflbm_batch* b, bool new_shape) {
   std::vector<FusedArgs> fa;
   std::vector<int2> wf;
   FusedPlan p;
-  if (fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+  if (b->fused_wanted && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
     for (int q = 0; q < 4; ++q)      // half q >> 1, launch parity q & 1
       for (int i = 0; i < count; ++i) {
         const nflbm_sim* m = b->members[i];
@@ -1352,6 +1377,16 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
   int rc = batch_half(b, &half);
   if (rc != NFLBM_OK) return rc;
   FusedPlan p;
+  if (nsteps >= 2 && !b->fused_wanted && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+    bool room = true;
+    for (nflbm_sim* m : b->members) room = room && fused_memory(m, b->stream);
+    if (room) {
+      b->fused_wanted = true;
+      rc = build_batch_tables(b, false);
+      if (rc != NFLBM_OK) return rc;
+      half = 0;
+    }
+  }
   if (nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
     const nflbm_sim* m0 = b->members[0];
     FusedLaunch f{};
@@ -1779,19 +1814,7 @@ int nflbm_create(const nflbm_config* cfg, nflbm_sim** out) {
   bool ok = hipGetDevice(&s->device) == hipSuccess;
   for (auto& a : state_arrays(s)) ok = ok && hipMalloc(a.first, a.second) == hipSuccess;
   const size_t psize = s->ts == 8 ? sizeof(DevParams<double>) : sizeof(DevParams<float>);
-  // the other record set of the fused steps lies behind the tables (one
-  // allocation less); without room for it the steps are taken one by one
-  FusedPlan fplan;
-  if (ok && fused_kind(s) && fused_plan(&s, 1, &fplan)) {
-    const size_t bytes = align_up(psize) + ((s->fform ? 8 : 0) + size_t(s->NE)) * n * s->rs;
-    if (hipMalloc(&s->params, bytes) == hipSuccess) {
-      s->fused_rec = static_cast<unsigned char*>(s->params) + align_up(psize);
-    } else {
-      s->params = nullptr;
-      (void)hipGetLastError();
-    }
-  }
-  ok = ok && (s->params || hipMalloc(&s->params, psize) == hipSuccess);
+  ok = ok && hipMalloc(&s->params, psize) == hipSuccess;
   ok = ok && hipMalloc(reinterpret_cast<void**>(&s->nanflag), sizeof(int)) == hipSuccess;
   ok = ok && hipHostMalloc(reinterpret_cast<void**>(&s->nan_host), sizeof(int), hipHostMallocDefault) == hipSuccess;
   ok = ok && hipEventCreateWithFlags(&s->nan_ev, hipEventDisableTiming) == hipSuccess;

@@ -69,7 +69,7 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, const DevParams<t
     const bool near = H <= a.nx && H <= a.ny;      // at most one wrap
     auto wrapped = [&](int v, int n) { return near ? v + (v < 0 ? n : (v >= n ? -n : 0)) : wrap(v, n); };
     const int gx = xin ? wrapped(x0 - H + lx, a.nx) : 0;
-    constexpr int U = sizeof(T) == 8 ? 2 : 3;
+    constexpr int U = sizeof(T) == 8 ? (NT == 768 ? 1 : 2) : 3;
     for (int row = lr; row < rows; row += U * RPP) {
       T cc[U][NE], mm[U][NE], vv[U][4], ff[U][4];
 #pragma unroll
@@ -460,10 +460,14 @@ hipError_t launch_shape(const FusedLaunch& f, hipStream_t s) {
 
 template <int NC, int ST>
 hipError_t launch_nc(const FusedLaunch& f, hipStream_t s) {
-  // the shapes fused_plan chooses from; 1024 threads leave 128 VGPRs each
+  // the shapes fused_plan chooses from; 1024 threads leave 128 VGPRs each, 768
+  // leave 168
   constexpr bool few = !(ST == kStoreF64 && NC >= 5);
   if (f.frecord && f.wlog2 == 5) {
     if (f.threads == 512) return launch_shape<NC, ST, true, 5, 512>(f, s);
+    if constexpr (ST == kStoreF64 && (NC == 5 || NC == 6)) {
+      if (f.threads == 768) return launch_shape<NC, ST, true, 5, 768>(f, s);
+    }
     if constexpr (few) {
       if (f.threads == 1024) return launch_shape<NC, ST, true, 5, 1024>(f, s);
     }

@@ -36,7 +36,9 @@ CASES = [
     ((250, 253), 4, "fp16s", PLAIN, 0.0, (0.0, 1e-6, 0.0)),    # 24 x 8
     ((515, 389), 3, "fp32", POT, 0.0, (0.0, 0.0, 0.0)),        # 24 x 24, 1024 threads
     ((419, 470), 5, "fp16s", POT, 0.05, (0.0, 0.0, 0.0)),      # 24 x 24, 512 threads
-    ((301, 150), 6, "fp64", PLAIN, 0.05, (0.0, 0.0, 0.0)),     # 24 x 16
+    ((301, 250), 6, "fp64", PLAIN, 0.05, (0.0, 0.0, 0.0)),     # 24 x 16, 768 threads
+    ((333, 299), 5, "fp64", POT, 0.0, (1e-6, 0.0, 0.0)),
+    ((301, 150), 7, "fp64", PLAIN, 0.05, (0.0, 0.0, 0.0)),     # 24 x 16, 512 threads
     ((170, 333), 8, "fp64", PLAIN, 0.0, (0.0, 0.0, 0.0)),      # the largest records
     ((90, 33), 7, "fp32", PLAIN, 0.0, (0.0, 0.0, 0.0)),
     ((700, 433), 4, "fp32", DIFF, 0.05, (0.0, 0.0, 0.0)),      # 56 x 24
