@@ -303,6 +303,10 @@ int nflbm_set_fields(nflbm_sim *sim, const double *C, const double *v, const dou
 
 /* Advance nsteps time steps (Sec. III: collide, stream, boundaries), each one
  * a reconstruction of C and one fused update launch on the sim's stream.
+ * Calls of two and more steps of a periodic D2Q9 lattice without solid nodes
+ * take several steps a launch where g and f are node records, where g is and
+ * f is not evolved, or where f is not evolved, every tau_g = 1 and the mobility
+ * depends on the concentrations; results do not depend on it.
  * Asynchronous: returns after queueing the work, without waiting for it.
  * NaN detection: on every K-th step (nflbm_set_nan_check, default K = 16)
  * the update raises a device flag where a node's C, mu~, v or P is not
@@ -418,7 +422,8 @@ int nflbm_coefficients(int N, const double *sigma, double D, double *alpha, doub
  * workgroup marches through zchunk planes (1 = a single plane) keeping three
  * planes of concentrations in LDS.  A value <= 0 keeps the current setting.
  * EINVAL if the shape is invalid or its LDS window exceeds the device limit.
- * Results do not depend on the shape.  nflbm_get_launch also reports the
+ * Results do not depend on the shape, and steps taken several a launch
+ * (nflbm_step) have tiles of their own.  nflbm_get_launch also reports the
  * device's LDS bytes per workgroup (any output pointer may be NULL).  The
  * default shape (chosen at nflbm_create, and again by nflbm_set_solid until
  * a shape is set here, by nflbm_set_conc_launch or by nflbm_autotune)
@@ -430,8 +435,8 @@ int nflbm_set_launch(nflbm_sim *sim, int tx_log2, int zchunk);
 int nflbm_get_launch(nflbm_sim *sim, int *tx_log2, int *zchunk, int *lds_limit);
 /* The same for the reconstruction kernel (zeroth moment of g, Sec. III B),
  * which has a launch shape of its own: in D3Q19 with g in the moment form it
- * marches along z with one plane of node records in LDS and defaults to
- * z runs that leave about 1024 workgroups, while the update keeps its own.
+ * marches along z with one plane of node records in LDS and has z runs of
+ * its own by default.
  * Results do not depend on it. */
 int nflbm_set_conc_launch(nflbm_sim *sim, int tx_log2, int zchunk);
 int nflbm_get_conc_launch(nflbm_sim *sim, int *tx_log2, int *zchunk);

@@ -380,10 +380,8 @@ StepArgs make_args(const nflbm_sim* s, int src);
 
 // Default shapes.  Update: tiles 64 x 4 (16 x 16 when nx <= 16 or when the
 // wider LDS window does not fit), in 3-D a z run per workgroup that leaves
-// about 8192 workgroups (4096 in the float record form of f, whose update
-// prefetches across the run: runs of 16 against 8 planes measured 0.303
-// against 0.314 ms at 256^3; 1024 in FP64, where longer runs measured
-// faster).
+// about 8192 workgroups (1024 in FP64, where longer runs measured faster), in
+// the record form of f a fitted one (below).
 // Reconstruction: the update's tile width; in the moment form's 3-D z march a
 // run that leaves about 1024 workgroups (each run re-loads two planes beyond
 // its ends, so long runs pay off as long as the CUs stay busy: 0.255 ms at

@@ -7,6 +7,15 @@
 // Every value is formed as k_conc_m and k_update form it, in the same order,
 // and records are rounded to their storage type after every step, so a run
 // does not depend on how its steps are split over the two paths.
+//
+// Float runs that fill the chip are bound by vector-ALU issue (82% busy over
+// 1740 x 1740, N = 3: 172 instructions of the reconstruction and 135 of the
+// update a node, times 1.6 for the halo and the lanes beyond a shrinking row),
+// FP64 at N = 6 by latency at three wavefronts a SIMD, small lattices by the
+// latency of the launch and of its phases.  Per step, two kernels against this
+// one: 64 x 64 FP64 N = 3 7.8 -> 3.0 us, nine 300 x 150 lenses FP64 N = 6
+// 61 -> 39 us, 32 lenses FP32 N = 3 (3.0 M nodes) 97 -> 61 us, 512 x 512 FP32
+// N = 4 10.1 -> 8.7 us, 2048 x 2048 FP32 N = 4 without the flow 88 -> 32 us.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

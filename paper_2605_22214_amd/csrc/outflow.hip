@@ -185,8 +185,10 @@ __device__ __forceinline__ void pull_g_all(const StepArgs& a, const Nbr& nb, uin
 // the first step: the source's record without a branch (a population bounced
 // back at a wall is the node's own opposite one, the record's with v and F
 // negated), so that a wavefront's directions are all in flight before the
-// first is used.  One at a time, each behind the last one's branches, they
-// were most of the outflow's time (see k_outflow_apply).
+// first is used.  Both kernels are bound by the latency of these scattered
+// loads: one direction at a time, each behind the last one's branches and the
+// sum for U, a 256 x 128 x 128 channel (N = 4, FP32) took 215 us a step, with
+// all in flight 211.
 template <class L, int NE, int ST>
 struct RecordPull {
   using S = StoreT<ST>;
