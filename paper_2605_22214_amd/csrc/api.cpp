@@ -806,19 +806,22 @@ int run_mob_steps(nflbm_sim* s, long long n, const FusedPlan& p, size_t lds, boo
   a.tile_h = (s->ny + ty - 1) / ty;
   ty = (s->ny + a.tile_h - 1) / a.tile_h;
   a.flags = s->step_flags;
-  while (n > 0) {
-    const int k = static_cast<int>(std::min<long long>(n, p.T));
+  // as many launches as leave the state in the set single steps would leave it
+  // in, so that a captured even number of steps can be replayed
+  long long launches = (n + p.T - 1) / p.T;
+  if ((launches ^ n) & 1) ++launches;
+  const auto launch = s->store == NFLBM_FP64 ? launch_fused_mob_0
+                                             : s->store == NFLBM_FP32 ? launch_fused_mob_1 : launch_fused_mob_2;
+  for (long long i = 0; i < launches; ++i) {
+    const int k = fused_count(n, launches, i);
     a.gk_src = s->gk[s->cur];
     a.g0_src = s->g0[s->cur];
     a.gk_dst = s->gk[s->cur ^ 1];
     a.g0_dst = s->g0[s->cur ^ 1];
     const uint32_t mask = nan_mask(s, k);
     if (mask) *checked = true;
-    const auto launch = s->store == NFLBM_FP64 ? launch_fused_mob_0
-                                               : s->store == NFLBM_FP32 ? launch_fused_mob_1 : launch_fused_mob_2;
     HIPCHK(s, launch(s->N, a, a.tiles_x * ty, k, mask, lds, s->stream));
     s->cur ^= 1;
-    n -= k;
   }
   return NFLBM_OK;
 }

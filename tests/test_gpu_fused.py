@@ -134,3 +134,32 @@ def test_fused_mobility_steps_report_nan():
     s.step(16)
     with pytest.raises(nf.NflbmError):
         s.synchronize()
+
+
+@pytest.mark.parametrize("flags,N", [(PLAIN, 3), (nf.FLAG_NO_HYDRO | nf.FLAG_C2C2_MOBILITY, 4)])
+def test_captured_fused_steps_replay(flags, N):
+    """An even number of steps captured into a graph advances the state by as
+    many on every replay, read-backs between them included."""
+    torch = pytest.importorskip("torch")
+    cfg = _config((70, 50), N, "fp32", flags)
+    a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+    C = _noise((70, 50), N, 4)
+    stream = torch.cuda.Stream()
+    b.set_stream(stream.cuda_stream)
+    for s in (a, b):
+        s.set_fields(C)
+        s.set_nan_check(0)
+    a.step(1)
+    b.step(1)
+    a.step(2)
+    b.step(2)                   # the fused steps' memory is there
+    stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        b.step(6)
+    for _ in range(3):
+        for _ in range(6):
+            a.step(1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(a.get_field("C"), b.get_field("C"))
