@@ -73,10 +73,10 @@ FORMS = {"fp32": ("fp32", 0), "fp16s": ("fp16s", 0), "fp64": ("fp64", 0),
 # instructions per lane (SQ_INSTS_VALU x 64 / nodes).  The committed summary
 # under profiles/ gives the commands and the raw figures.
 COUNTERS = {
-    "sources_sha256": "f5a4a75617dd70ce87baa1ceaa11e9742b19be83592075ee1b06db4ead167beb",
+    "sources_sha256": "3934672bb8852847e23efa0d1c33cb69a56ded3dbb3a899cafaeb783296748ab",
     "n": 256,
-    "k_update": {"fp32": (87.1, 387.1), "fp16s": (55.1, 414.1), "fp64": (171.2, 452.0)},
-    "k_conc_m": {"fp32": (104.5, 462.4), "fp16s": (70.2, 518.2), "fp64": (218.4, 587.0)},
+    "k_update": {"fp32": (85.0, 382.5), "fp16s": (53.0, 409.5), "fp64": (170.4, 433.3)},
+    "k_conc_m": {"fp32": (104.0, 461.6), "fp16s": (71.5, 515.7), "fp64": (232.8, 559.4)},
 }
 # VALU issue peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (one lane-op per
 # lane and cycle; packed FP32 is not generated by these builds).
