@@ -81,6 +81,9 @@ struct nflbm_sim {
   void* frec = nullptr;
   void* fmom = nullptr;
   bool f_local = false;
+  // diffusive-only runs: the velocity records may not be those of rest (they
+  // came with a state); the next step reads them and leaves those of rest
+  bool vel_given = false;
   // open faces: FaceBC<T> on the device, and the host's copy of each face
   void* faces = nullptr;
   int open_mask = 0;
@@ -615,6 +618,7 @@ int launch_step(nflbm_sim* s, hipEvent_t ev0, hipEvent_t ev1, bool* checked = nu
   if (s->c2c2) HIPCHK(s, launch_mob_source(s->lat, s->N, s->store, mob_args(s, a), s->stream));
   s->cur ^= 1;
   s->f_local = false;   // from now on every f streams in from its neighbour
+  s->vel_given = false;
   if (s->out_face >= 0) return launch_outflow_step(s, 0);
   return NFLBM_OK;
 }
@@ -685,13 +689,15 @@ bool fused_plan(const nflbm_sim* const* m, size_t count, FusedPlan* out) {
 
 // Whether the configuration can take fused steps at all (node records of a
 // periodic D2Q9 lattice, f as records too or not evolved), and whether it
-// can now (no solid nodes).
+// can now (no solid nodes, and records that a single step reads in full: the
+// fused diffusive-only steps take the velocities as 0).
 bool fused_kind(const nflbm_sim* s) {
   return s->lat == NFLBM_D2Q9 && s->gform && (s->fform || (s->step_flags & kFlagNoHydro)) && !s->wall[0] &&
          !s->wall[1];
 }
-bool fused_now(const nflbm_sim* s) { return fused_kind(s) && !s->bb && s->out_face < 0 && !s->f_local; }
-
+bool fused_now(const nflbm_sim* s) {
+  return fused_kind(s) && !s->bb && s->out_face < 0 && !s->f_local && !s->vel_given;
+}
 
 // Memory for the other record set of the fused steps: the read-back fields'
 // buffer, which a run that is looked at has anyway (a buffer of its own made
@@ -829,7 +835,7 @@ int run_mob_steps(nflbm_sim* s, long long n, const FusedPlan& p, size_t lds, boo
 // n steps of s on its stream; *checked is set when one of them checked for
 // non-finite values.
 int run_steps(nflbm_sim* s, long long n, bool* checked) {
-  for (; n > 0 && s->f_local; --n) {
+  for (; n > 0 && (s->f_local || s->vel_given); --n) {
     const int rc = launch_step(s, nullptr, nullptr, checked);
     if (rc != NFLBM_OK) return rc;
   }
@@ -1363,7 +1369,7 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
     BHIPCHK(b, launch_half(b, 0));
     for (nflbm_sim* m : b->members) {
       m->cur ^= 1;
-      m->f_local = false;
+      m->f_local = m->vel_given = false;
     }
     rc = build_batch_tables(b, false);
     if (rc != NFLBM_OK) return rc;
@@ -1389,6 +1395,16 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
     }
   }
   if (nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+    bool given = false;
+    for (const nflbm_sim* m : b->members) given = given || m->vel_given;
+    if (given) {      // this step reads the velocities (see fused_now)
+      BHIPCHK(b, launch_half(b, half));
+      for (nflbm_sim* m : b->members) {
+        m->cur ^= 1;
+        m->vel_given = false;
+      }
+      return batch_run(b, nsteps - 1, mode);
+    }
     const nflbm_sim* m0 = b->members[0];
     FusedLaunch f{};
     f.params = b->params;
@@ -1432,6 +1448,7 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
   if (nsteps & 1)
     for (nflbm_sim* m : b->members) m->cur ^= 1;
   if (nsteps > 0) {
+    for (nflbm_sim* m : b->members) m->vel_given = false;
     BHIPCHK(b, nan_enqueue(b->nanflag, b->nan_host, b->nan_ev, b->stream));
     b->nan_pending = true;
   }
@@ -1506,12 +1523,13 @@ std::string sim_key(const nflbm_sim* s) {
 struct SavedState {
   std::vector<void*> copies;
   int cur = 0;
-  bool f_local = false;
+  bool f_local = false, vel_given = false;
 };
 
 int save_state(nflbm_sim* s, SavedState* st) {
   st->cur = s->cur;
   st->f_local = s->f_local;
+  st->vel_given = s->vel_given;
   for (const auto& seg : state_segments(s)) {
     void* c = nullptr;
     if (hipMalloc(&c, seg.second) != hipSuccess) return fail(s, NFLBM_ENOMEM, "cannot allocate the autotuner's state copy");
@@ -1524,6 +1542,7 @@ int save_state(nflbm_sim* s, SavedState* st) {
 int restore_state(nflbm_sim* s, SavedState* st) {
   s->cur = st->cur;
   s->f_local = st->f_local;
+  s->vel_given = st->vel_given;
   const auto segs = state_segments(s);
   hipError_t e = hipSuccess;
   for (size_t i = 0; i < st->copies.size() && i < segs.size() && e == hipSuccess; ++i)
@@ -2152,6 +2171,7 @@ int nflbm_set_fields(nflbm_sim* sim, const double* C, const double* v, const dou
   // record, which the population form stores at every node; g entering
   // across an open face is the initial 0)
   sim->f_local = sim->gform != 0;
+  sim->vel_given = false;
   return sim_nan_reset(sim);
 }
 
@@ -2509,6 +2529,7 @@ int nflbm_set_state(nflbm_sim* sim, const void* host_raw) {
     p += seg.second;
   }
   if (state_tail(sim)) sim->f_local = *p != 0;
+  sim->vel_given = sim->gform && (sim->step_flags & kFlagNoHydro);
   const int rc = refresh_outflow_plane(sim);
   if (rc) return rc;
   HIPCHK(sim, hipStreamSynchronize(sim->stream));

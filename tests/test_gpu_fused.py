@@ -163,3 +163,30 @@ def test_captured_fused_steps_replay(flags, N):
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(a.get_field("C"), b.get_field("C"))
+
+
+@pytest.mark.parametrize("batch", [False, True])
+def test_restored_velocities_advect_one_step(batch):
+    """A state of a run with flow, restored where the flow is not evolved:
+    its velocities act on the first step, as they do in single steps."""
+    shape, N = (70, 50), 3
+    cfg = _config(shape, N, "fp32", DIFF)
+    with nf.Simulation(**_config(shape, N, "fp32", nf.FLAG_F_POPULATIONS)) as flow:
+        v = np.zeros((3, 1, shape[1], shape[0]))
+        v[0] = 0.02 * np.random.default_rng(5).uniform(-1.0, 1.0, size=v.shape[1:])
+        flow.set_fields(_noise(shape, N, 5), v)
+        flow.step(3)
+        raw = flow.get_state()
+    a = nf.Simulation(**cfg)
+    b = nf.Batch([cfg]) if batch else nf.Simulation(**cfg)
+    s = b.members[0] if batch else b
+    for warm in (a, s):
+        warm.set_fields(_noise(shape, N, 6))
+    a.step(2)
+    b.step(2)
+    a.set_state(raw)
+    s.set_state(raw)
+    for _ in range(7):
+        a.step(1)
+    b.step(7)
+    _same(a, s)
