@@ -759,8 +759,10 @@ hipError_t launch_fused(const nflbm_sim* s, const FusedLaunch& f, hipStream_t st
   }
 }
 
-// An even number of launches for n >= 2 steps, so that the state ends in the
-// primary records: launch i takes fused_count(n, launches, i) steps.
+// An even number of launches for an even n >= 2 of steps, so that the state
+// ends in the primary records and in the C set where single steps leave it (a
+// captured call can then be replayed after any others): launch i takes
+// fused_count(n, launches, i) steps.
 long long fused_launches(long long n, int T) { return 2 * ((n + 2 * T - 1) / (2 * T)); }
 int fused_count(long long n, long long launches, long long i) {
   return static_cast<int>(n / launches + (i < n % launches ? 1 : 0));
@@ -843,7 +845,7 @@ int run_steps(nflbm_sim* s, long long n, bool* checked) {
   size_t lds = 0;
   if (n >= 2 && fused_mob_now(s) && fused_mob_plan(s, &p, &lds)) return run_mob_steps(s, n, p, lds, checked);
   if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p) && fused_memory(s, s->stream)) {
-    if (fused_launches(n, p.T) > n) {      // one step a launch, an odd number
+    if (n & 1) {      // one by the two kernels, for the parity of C's sets
       const int rc = launch_step(s, nullptr, nullptr, checked);
       if (rc != NFLBM_OK) return rc;
       --n;
@@ -1414,7 +1416,7 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
     f.threads = p.threads;
     f.blocks = b->blocks_fused;
     f.lds = fused_lds(m0, p);
-    if (fused_launches(nsteps, p.T) > nsteps) {   // one step a launch, an odd number
+    if (nsteps & 1) {   // one by the two kernels, for the parity of C's sets
       BHIPCHK(b, launch_half(b, half));
       for (nflbm_sim* m : b->members) m->cur ^= 1;
       half ^= 1;

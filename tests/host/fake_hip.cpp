@@ -168,7 +168,9 @@ hipError_t launch_update(int, int nc, int, const StepArgs& a, bool fields, hipSt
   return record(fields ? "fields" : "update", &a);
 }
 hipError_t launch_init(int, int, int, const InitArgs&, hipStream_t) { return record("init"); }
-hipError_t launch_batch_step(int, int, int, const BatchLaunch&, hipStream_t) { return record("batch"); }
+hipError_t launch_batch_step(int, int, int, const BatchLaunch& b, hipStream_t) {
+  return record("batch", b.args);
+}
 hipError_t launch_expand(int, int, int, const StepArgs&, hipStream_t) { return record("expand"); }
 int groups_per_cu(int, int, int, const StepArgs&, bool) { return 0; }
 size_t conc_m_lds_bytes(int, int, int, int, bool) { return 32 << 10; }

@@ -14,7 +14,7 @@ namespace fake {
 
 struct Launch {
   std::string kind;           // conc, update, fields, fused2d, fused_mob, batch, ...
-  nflbm::StepArgs step{};     // of conc, update, fields
+  nflbm::StepArgs step{};     // of conc, update, fields; the first member's of batch
   nflbm::FusedArgs fused{};   // of a fused2d launch of one simulation
   nflbm::FusedLaunch shape{};
   int nsteps = 0;             // of fused launches

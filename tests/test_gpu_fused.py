@@ -190,3 +190,33 @@ def test_restored_velocities_advect_one_step(batch):
         a.step(1)
     b.step(7)
     _same(a, s)
+
+
+def test_captured_step_replays_after_odd_calls():
+    """A captured pair of single steps advances the state after calls of any
+    lengths that add up to an even number."""
+    torch = pytest.importorskip("torch")
+    cfg = _config((70, 50), 3, "fp32")
+    a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+    stream = torch.cuda.Stream()
+    b.set_stream(stream.cuda_stream)
+    for s in (a, b):
+        s.set_fields(_noise((70, 50), 3, 4))
+        s.set_nan_check(0)
+        s.step(1)
+        s.step(1)
+    stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        b.step(1)
+        b.step(1)
+    total = 0
+    for n in (3, 5, 7):
+        b.step(n)
+        b.step(1)
+        with torch.cuda.stream(stream):
+            g.replay()
+        total += n + 3
+    for _ in range(total):
+        a.step(1)
+    assert np.array_equal(a.get_field("C"), b.get_field("C"))
