@@ -414,7 +414,10 @@ __device__ __forceinline__ void fused_tile(const FusedArgs& a, const DevParams<t
           const T cP = T(3) * Pn;
           const T fB = static_cast<T>(fma(-T(1.5), vF, cP));
           if (last) {
-            const T vel[4] = {v[0], v[1], v[2], base_s};
+            // a resting node's -3/2 v.v is -0, which the update's conversion to
+            // binary16 (a fused multiply-add onto 0) stores as +0
+            constexpr bool HALF = sizeof(typename S::RS) != sizeof(T);
+            const T vel[4] = {v[0], v[1], v[2], HALF ? base_s + T(0) : base_s};
             const T fr[4] = {fB, F[0], F[1], F[2]};
             rec_store<S, 4, false>(a.vel_dst, node * 4, vel, T(S::vel_scale));
             rec_store<S, 4, false>(a.frec_dst, node * 4, fr, T(S::vel_scale));

@@ -220,3 +220,19 @@ def test_captured_step_replays_after_odd_calls():
     for _ in range(total):
         a.step(1)
     assert np.array_equal(a.get_field("C"), b.get_field("C"))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16s"])
+@pytest.mark.parametrize("N", range(2, 9))
+def test_resting_state_keeps_its_bytes(N, precision):
+    """At rest -3/2 v.v is a zero, whose sign binary16 records hold as the
+    two kernels store it: the checkpoint's bytes do not depend on the split."""
+    for flags, omega in ((PLAIN, 0.0), (PLAIN, 0.05), (POT, 0.0), (POT, 0.05), (DIFF, 0.0)):
+        cfg = _config((40, 33), N, precision, flags, omega)
+        a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+        for s in (a, b):
+            s.set_fields(np.full((N, 1, 33, 40), 1.0 / N))
+        for _ in range(9):
+            a.step(1)
+        b.step(9)
+        assert np.array_equal(a.get_state(), b.get_state()), (flags, omega)
