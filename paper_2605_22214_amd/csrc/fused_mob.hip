@@ -223,7 +223,9 @@ __global__ void __launch_bounds__(512) k_fused_mob(FusedMobArgs ma, int nsteps, 
           FS v[NE];
 #pragma unroll
           for (int i = 0; i < NE; ++i) {
-            v[i] = S::pack(wk * proj<L>(k, G[i]));
+            // the general path adds the source to the population its update
+            // left, a zero: a source of -0 is stored as +0
+            v[i] = S::pack(T(0) + wk * proj<L>(k, G[i]));
             moved[i] += S::unpack(v[i]);
           }
           if (last) vst<FS, NE>(at(static_cast<FS*>(ma.gk_dst) + size_t(k - 1) * gst, node * NE), v);

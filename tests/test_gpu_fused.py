@@ -229,10 +229,24 @@ def test_resting_state_keeps_its_bytes(N, precision):
     two kernels store it: the checkpoint's bytes do not depend on the split."""
     for flags, omega in ((PLAIN, 0.0), (PLAIN, 0.05), (POT, 0.0), (POT, 0.05), (DIFF, 0.0)):
         cfg = _config((40, 33), N, precision, flags, omega)
-        a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
-        for s in (a, b):
-            s.set_fields(np.full((N, 1, 33, 40), 1.0 / N))
-        for _ in range(9):
-            a.step(1)
-        b.step(9)
-        assert np.array_equal(a.get_state(), b.get_state()), (flags, omega)
+        _resting_bytes(cfg, N, (flags, omega))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16s"])
+@pytest.mark.parametrize("N", range(2, 9))
+def test_resting_mobility_state_keeps_its_bytes(N, precision):
+    """The same where the source terms are zeros of either sign."""
+    for omega in (0.0, 0.05):
+        cfg = _config((40, 33), N, precision, DIFF | nf.FLAG_C2C2_MOBILITY, omega)
+        cfg["m"] = 10.0
+        _resting_bytes(cfg, N, omega)
+
+
+def _resting_bytes(cfg, N, case):
+    a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+    for s in (a, b):
+        s.set_fields(np.full((N, 1, 33, 40), 1.0 / N))
+    for _ in range(9):
+        a.step(1)
+    b.step(9)
+    assert np.array_equal(a.get_state(), b.get_state()), case
