@@ -307,7 +307,10 @@ int nflbm_set_fields(nflbm_sim *sim, const double *C, const double *v, const dou
  * take several steps a launch where g and f are node records, where g is and
  * f is not evolved, or where f is not evolved, every tau_g = 1 and the mobility
  * depends on the concentrations; results do not depend on it.
- * Asynchronous: returns after queueing the work, without waiting for it.
+ * Asynchronous: returns after queueing the work, without waiting for it, and
+ * allocates nothing.  Captured into a graph, an even number of steps advances
+ * the state by as many on every replay, as long as the steps taken between
+ * replays add up to an even number.
  * NaN detection: on every K-th step (nflbm_set_nan_check, default K = 16)
  * the update raises a device flag where a node's C, mu~, v or P is not
  * finite, and nflbm_step queues a copy of that flag to host memory behind
@@ -346,8 +349,13 @@ int nflbm_step_timed_kernels(nflbm_sim *sim, long long nsteps, double *ms_conc, 
 int nflbm_get_field(nflbm_sim *sim, int field, double *host_out);
 
 /* Device memory the state of a simulation with configuration cfg occupies
- * (every array the steps read or write: both f sets, g or the node records,
- * the reconstructed C and E_B), each array rounded up to 256 bytes.  Host-only
+ * (both f sets, g or the node records, the reconstructed C and E_B), each
+ * array rounded up to 256 bytes.  Besides it nflbm_create allocates the
+ * scratch of the concentration-dependent mobility (N values a node) and, for
+ * the D2Q9 runs that take several steps a launch through node records (see
+ * nflbm_step), a second set of them: (8 + N - 1) record values a node, N - 1
+ * where f is not evolved.  Without room for that set such a run steps through
+ * two kernels.  Host-only
  * planning: validates cfg as nflbm_create does (same errors), allocates
  * nothing.  For callers that provide the memory, e.g. a torch tensor. */
 int nflbm_device_bytes(const nflbm_config *cfg, size_t *bytes);

@@ -124,8 +124,10 @@ struct nflbm_sim {
   unsigned boundary_version = 0;
   void* eb = nullptr;
   void* params = nullptr;
-  // read-back fields [2N+7][n], made on first use; between read-backs the other
-  // record set of the fused steps (fused_args)
+  // the other record set of the fused steps (fused_args), made at creation;
+  // null where they cannot be taken or there was no memory for it
+  unsigned char* other = nullptr;
+  // read-back fields [2N+7][n], made on first use
   double* fields = nullptr;
   double* red = nullptr;
   // read-back of large fields: pinned slots the device copies into and the
@@ -178,7 +180,6 @@ struct nflbm_batch {
   FusedArgs* fargs = nullptr;
   int2* work_fused = nullptr;
   int blocks_fused = 0;
-  bool fused_wanted = false;   // from the first steps that can be fused on
   std::vector<int> key;     // member parities that args[0..count) was built for
   std::vector<unsigned> versions;   // members' boundary_version at that build
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -283,6 +284,8 @@ void free_device(nflbm_sim* s) {
     }
   }
   s->stage = nullptr;
+  if (s->other) (void)hipFree(s->other);
+  s->other = nullptr;
   if (s->fields) (void)hipFree(s->fields);
   if (s->red) (void)hipFree(s->red);
   s->params = s->eb = nullptr;
@@ -696,37 +699,19 @@ bool fused_kind(const nflbm_sim* s) {
          !s->wall[1];
 }
 bool fused_now(const nflbm_sim* s) {
-  return fused_kind(s) && !s->bb && s->out_face < 0 && !s->f_local && !s->vel_given;
+  return fused_kind(s) && s->other && !s->bb && s->out_face < 0 && !s->f_local && !s->vel_given;
 }
 
-// Memory for the other record set of the fused steps: the read-back fields'
-// buffer, which a run that is looked at has anyway (a buffer of its own made
-// nflbm_create a third slower).  False where there is none to be had, or none
-// yet while the stream is being captured: the steps are then taken one by one.
-bool fused_memory(nflbm_sim* s, hipStream_t stream) {
-  if (s->fields) return true;
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  if (st != hipStreamCaptureStatusNone) return false;
-  if (hipMalloc(reinterpret_cast<void**>(&s->fields), size_t(2 * s->N + 7) * s->n * sizeof(double)) != hipSuccess) {
-    s->fields = nullptr;
-    (void)hipGetLastError();
-    return false;
-  }
-  return true;
-}
+// Bytes of the other record set of the fused steps: (8 + NE) record values a
+// node with the flow (v, the f record, mu~), mu~ alone without.
+size_t fused_other_bytes(const nflbm_sim* s) { return ((s->fform ? 8 : 0) + size_t(s->NE)) * s->n * s->rs; }
 
 // Arguments of a fused launch from C set `cur`: from the primary records to
-// the others (odd = 0) or back.  The others, (8 + NE) record values a node
-// (v, the f record, mu~), lie in the read-back fields' buffer, whose contents
-// no call leaves behind.
+// the others (odd = 0) or back, whose contents no call leaves behind.
 FusedArgs fused_args(const nflbm_sim* s, const FusedPlan& p, int cur, int odd) {
   FusedArgs a{};
   const size_t n = s->n;
-  unsigned char* o = reinterpret_cast<unsigned char*>(s->fields);
+  unsigned char* o = s->other;
   void* rec[2][3] = {{s->mu, s->vel, s->frec}, {o, o, o}};
   if (s->fform) {
     rec[1][0] = o + 8 * n * s->rs;
@@ -844,7 +829,7 @@ int run_steps(nflbm_sim* s, long long n, bool* checked) {
   FusedPlan p;
   size_t lds = 0;
   if (n >= 2 && fused_mob_now(s) && fused_mob_plan(s, &p, &lds)) return run_mob_steps(s, n, p, lds, checked);
-  if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p) && fused_memory(s, s->stream)) {
+  if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p)) {
     if (n & 1) {      // one by the two kernels, for the parity of C's sets
       const int rc = launch_step(s, nullptr, nullptr, checked);
       if (rc != NFLBM_OK) return rc;
@@ -1164,7 +1149,7 @@ void free_batch_tables(nflbm_batch* b) {
 // Whether every member can take fused steps, all in one record form.
 bool fused_batch(const nflbm_batch* b) {
   for (const nflbm_sim* m : b->members)
-    if (!fused_kind(m) || m->bb || m->out_face >= 0 || m->fform != b->members[0]->fform) return false;
+    if (!fused_kind(m) || !m->other || m->bb || m->out_face >= 0 || m->fform != b->members[0]->fform) return false;
   return true;
 }
 
@@ -1218,7 +1203,7 @@ int build_batch_tables(nflbm_batch* b, bool new_shape) {
   std::vector<FusedArgs> fa;
   std::vector<int2> wf;
   FusedPlan p;
-  if (b->fused_wanted && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+  if (fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
     for (int q = 0; q < 4; ++q)      // half q >> 1, launch parity q & 1
       for (int i = 0; i < count; ++i) {
         const nflbm_sim* m = b->members[i];
@@ -1386,16 +1371,6 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
   int rc = batch_half(b, &half);
   if (rc != NFLBM_OK) return rc;
   FusedPlan p;
-  if (nsteps >= 2 && !b->fused_wanted && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
-    bool room = true;
-    for (nflbm_sim* m : b->members) room = room && fused_memory(m, b->stream);
-    if (room) {
-      b->fused_wanted = true;
-      rc = build_batch_tables(b, false);
-      if (rc != NFLBM_OK) return rc;
-      half = 0;
-    }
-  }
   if (nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
     bool given = false;
     for (const nflbm_sim* m : b->members) given = given || m->vel_given;
@@ -1845,6 +1820,10 @@ int nflbm_create(const nflbm_config* cfg, nflbm_sim** out) {
     ok = ok && hipMalloc(&s->mob, msize) == hipSuccess;
     ok = ok && hipMalloc(&s->phi, size_t(N) * n * s->ts) == hipSuccess;
   }
+  if (ok && fused_kind(s) && hipMalloc(reinterpret_cast<void**>(&s->other), fused_other_bytes(s)) != hipSuccess) {
+    s->other = nullptr;          // its steps are then taken one by one
+    (void)hipGetLastError();
+  }
   if (!ok) {
     free_device(s);
     delete s;
@@ -2130,9 +2109,17 @@ int nflbm_set_fields(nflbm_sim* sim, const double* C, const double* v, const dou
     P = Pshift.data();
   }
   const size_t cnt = size_t(sim->N) * n + (v ? 3 * n : 0) + (P ? n : 0);
+  // uploaded into the other record set of the fused steps where that is large
+  // enough (no call leaves anything there), which spares an allocation
   double* tmp = nullptr;
-  if (hipMalloc(reinterpret_cast<void**>(&tmp), cnt * sizeof(double)) != hipSuccess)
-    return fail(sim, NFLBM_ENOMEM, "cannot allocate the initialisation buffer");
+  double* own = nullptr;
+  if (sim->other && cnt * sizeof(double) <= fused_other_bytes(sim)) {
+    tmp = reinterpret_cast<double*>(sim->other);
+  } else {
+    if (hipMalloc(reinterpret_cast<void**>(&own), cnt * sizeof(double)) != hipSuccess)
+      return fail(sim, NFLBM_ENOMEM, "cannot allocate the initialisation buffer");
+    tmp = own;
+  }
   double* dC = tmp;
   double* dv = v ? tmp + size_t(sim->N) * n : nullptr;
   double* dP = P ? tmp + size_t(sim->N) * n + (v ? 3 * n : 0) : nullptr;
@@ -2161,12 +2148,12 @@ int nflbm_set_fields(nflbm_sim* sim, const double* C, const double* v, const dou
     const int rc = launch_outflow_step(sim, 1);
     if (rc) {
       (void)hipStreamSynchronize(sim->stream);
-      (void)hipFree(tmp);
+      (void)hipFree(own);
       return rc;
     }
   }
   if (e == hipSuccess) e = hipStreamSynchronize(sim->stream);
-  (void)hipFree(tmp);
+  (void)hipFree(own);
   if (e != hipSuccess) return hip_fail(sim, e, "set_fields");
   // moment form: the first step starts from the initial populations (the
   // record form of f takes each node's f as the equilibrium of its own

@@ -23,7 +23,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   std::lock_guard<std::mutex> lk(fake::mx);
   ++state().mallocs;
   *p = nullptr;
-  if (state().device_bytes() + n > state().device_limit) return hipErrorOutOfMemory;
+  if (n == state().fail_at) return hipErrorOutOfMemory;
   if (posix_memalign(p, 256, n ? n : 256)) return hipErrorOutOfMemory;
   std::memset(*p, 0, n);
   state().device[*p] = n;

@@ -25,7 +25,7 @@ struct State {
   std::map<void*, size_t> device, pinned;   // live allocations
   long long mallocs = 0, syncs = 0;         // hipMalloc and hipStreamSynchronize calls
   long long events = 0;                     // live events
-  size_t device_limit = ~size_t(0);         // a hipMalloc beyond it fails
+  size_t fail_at = 0;                       // a hipMalloc of this size fails
   bool pinned_fails = false;                // hipHostMalloc fails
   bool capturing = false;                   // hipStreamIsCapturing
 

@@ -98,10 +98,80 @@ static void state_parity() {
   nflbm_batch_destroy(b);
 }
 
+// Stepping queues launches: it allocates nothing, and a batch waits for
+// nothing once the first step after set_fields is done.
+static void stepping_allocates_nothing() {
+  const int forms[] = {0, NFLBM_FLAG_NO_HYDRO, NFLBM_FLAG_NO_HYDRO | NFLBM_FLAG_C2C2_MOBILITY, NFLBM_FLAG_F_POPULATIONS};
+  for (int flags : forms)
+    for (int precision : {NFLBM_FP64, NFLBM_FP32, NFLBM_FP16S}) {
+      Problem p(NFLBM_D2Q9, 70, 50, 1, 3, precision, flags);
+      nflbm_sim* s = make(p);
+      nflbm_batch* b = nullptr;
+      CHECK(nflbm_batch_create(&p.cfg, 1, &b) == NFLBM_OK);
+      std::vector<double> C(3 * 70 * 50, 1.0 / 3.0), out(C.size());
+      CHECK(nflbm_set_fields(s, C.data(), nullptr, nullptr) == NFLBM_OK);
+      CHECK(nflbm_batch_set_fields(b, 0, C.data(), nullptr, nullptr) == NFLBM_OK);
+      for (bool read : {false, true}) {
+        if (read) {
+          CHECK(nflbm_get_field(s, NFLBM_FIELD_C, out.data()) == NFLBM_OK);
+          CHECK(nflbm_batch_get_field(b, 0, NFLBM_FIELD_C, out.data()) == NFLBM_OK);
+        }
+        long long before = state().mallocs;
+        CHECK(nflbm_step(s, 1) == NFLBM_OK && nflbm_step(s, 9) == NFLBM_OK);
+        CHECK(nflbm_batch_step(b, 1, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+        CHECK(state().mallocs == before);
+        const long long waits = state().syncs;
+        CHECK(nflbm_batch_step(b, 9, NFLBM_BATCH_LAUNCH) == NFLBM_OK && nflbm_batch_step(b, 2, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+        CHECK(state().mallocs == before && state().syncs == waits);
+        double ms = 0.0;
+        CHECK(nflbm_step_timed(s, 6, &ms, nullptr) == NFLBM_OK);
+        CHECK(state().mallocs == before);
+      }
+      nflbm_destroy(s);
+      nflbm_batch_destroy(b);
+    }
+  CHECK(state().count("fused2d") > 0 && state().count("fused2d_batch") > 0 && state().count("fused_mob") > 0);
+  CHECK(state().device.empty() && state().pinned.empty() && state().events == 0);
+}
+
+// The other record set of the fused steps: no more than its values, and a
+// simulation without room for it steps through the two kernels.
+static void other_record_set() {
+  for (int N = 2; N <= 8; ++N)
+    for (int precision : {NFLBM_FP64, NFLBM_FP32, NFLBM_FP16S}) {
+      Problem p(NFLBM_D2Q9, 128, 96, 1, N, precision);
+      const size_t n = 128 * 96, rs = precision == NFLBM_FP64 ? 8 : (precision == NFLBM_FP32 ? 4 : 2);
+      size_t planned = 0;
+      CHECK(nflbm_device_bytes(&p.cfg, &planned) == NFLBM_OK);
+      nflbm_sim* s = make(p);
+      const size_t used = state().device_bytes();
+      CHECK(nflbm_step(s, 1) == NFLBM_OK && nflbm_step(s, 8) == NFLBM_OK);
+      CHECK(state().count("fused2d") > 0);
+      CHECK(state().device_bytes() == used);
+      CHECK(used <= planned + (8 + size_t(N - 1)) * n * rs + (64 << 10));
+      nflbm_destroy(s);
+    }
+  state().launches.clear();
+  Problem p(NFLBM_D2Q9, 128, 96, 1, 3, NFLBM_FP64);
+  state().fail_at = (8 + 2) * size_t(128 * 96) * 8;
+  nflbm_sim* s = make(p);
+  nflbm_batch* b = nullptr;
+  CHECK(nflbm_batch_create(&p.cfg, 1, &b) == NFLBM_OK);
+  state().fail_at = 0;
+  const long long before = state().mallocs;
+  CHECK(nflbm_step(s, 9) == NFLBM_OK && nflbm_batch_step(b, 9, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+  CHECK(state().mallocs == before);
+  CHECK(state().count("conc") == 9 && state().count("batch") == 9);
+  nflbm_destroy(s);
+  nflbm_batch_destroy(b);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
   else if (name == "state_parity") state_parity();
+  else if (name == "stepping_allocates_nothing") stepping_allocates_nothing();
+  else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());
     return 2;

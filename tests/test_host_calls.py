@@ -12,7 +12,7 @@ CSRC = os.path.join(ROOT, "paper_2605_22214_amd", "csrc")
 HOST = os.path.join(ROOT, "tests", "host")
 CLANG = "/opt/rocm/llvm/bin/clang++"
 
-CHECKS = ["restored_velocities", "state_parity"]
+CHECKS = ["restored_velocities", "state_parity", "stepping_allocates_nothing", "other_record_set"]
 
 
 @pytest.fixture(scope="module")
