@@ -537,7 +537,8 @@ int nflbm_batch_set_launch(nflbm_batch *b, int tx_log2, int graph_steps);
 int nflbm_batch_get_launch(nflbm_batch *b, int *tx_log2, int *graph_steps, int *blocks_update);
 /* Total lattice nodes over all members. */
 int nflbm_batch_nodes(const nflbm_batch *b, long long *nodes);
-/* Autotuner of the batch tile width (graph mode), as nflbm_autotune; the cache
+/* Autotuner of the batch tile width (the two kernels in graph mode, also
+ * where nflbm_batch_step takes several steps a launch), as nflbm_autotune; the cache
  * key adds the member count, node total and a hash of the member shapes. */
 int nflbm_batch_autotune(nflbm_batch *b, const char *cache_path);
 /* Message of the last error on b (of the calling thread if b is NULL). */

@@ -1326,7 +1326,8 @@ int capture_graph(nflbm_batch* b, int half) {
   return NFLBM_OK;
 }
 
-int batch_run(nflbm_batch* b, long long nsteps, int mode) {
+// fuse = false keeps to the two kernels (the autotuner times those).
+int batch_run(nflbm_batch* b, long long nsteps, int mode, bool fuse = true) {
   if (mode == NFLBM_BATCH_PER_SIM) {
     for (nflbm_sim* m : b->members) {
       const int rc = nflbm_step(m, nsteps);
@@ -1365,13 +1366,13 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
       b->nan_pending = true;
       return NFLBM_OK;
     }
-    return batch_run(b, nsteps - 1, mode);
+    return batch_run(b, nsteps - 1, mode, fuse);
   }
   int half = 0;
   int rc = batch_half(b, &half);
   if (rc != NFLBM_OK) return rc;
   FusedPlan p;
-  if (nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+  if (fuse && nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
     bool given = false;
     for (const nflbm_sim* m : b->members) given = given || m->vel_given;
     if (given) {      // this step reads the velocities (see fused_now)
@@ -1380,7 +1381,7 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
         m->cur ^= 1;
         m->vel_given = false;
       }
-      return batch_run(b, nsteps - 1, mode);
+      return batch_run(b, nsteps - 1, mode, fuse);
     }
     const nflbm_sim* m0 = b->members[0];
     FusedLaunch f{};
@@ -1430,6 +1431,27 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode) {
     b->nan_pending = true;
   }
   return NFLBM_OK;
+}
+
+// batch_run between two events, and its device time.
+int batch_timed(nflbm_batch* b, long long nsteps, int mode, double* ms, bool fuse) {
+  hipEvent_t e0, e1;
+  BHIPCHK(b, hipEventCreate(&e0));
+  BHIPCHK(b, hipEventCreate(&e1));
+  BHIPCHK(b, hipEventRecord(e0, b->stream));
+  int rc = batch_run(b, nsteps, mode, fuse);
+  if (rc == NFLBM_OK) {
+    BHIPCHK(b, hipEventRecord(e1, b->stream));
+    BHIPCHK(b, hipEventSynchronize(e1));
+    float t = 0.f;
+    BHIPCHK(b, hipEventElapsedTime(&t, e0, e1));
+    *ms = t;
+    BHIPCHK(b, nan_poll(&b->nan_pending, &b->nan_seen, b->nan_host, b->nan_ev, true));
+    if (b->nan_seen) rc = bfail(b, NFLBM_ENUMERIC, "a NaN or Inf appeared in a member's state");
+  }
+  (void)hipEventDestroy(e0);
+  (void)hipEventDestroy(e1);
+  return rc;
 }
 
 // Clear the batch's NaN flag (a member's state was set anew).
@@ -2816,23 +2838,7 @@ int nflbm_batch_step_timed(nflbm_batch* b, long long nsteps, int mode, double* m
   if (nsteps < 0) return bfail(b, NFLBM_EINVAL, "nsteps < 0");
   if (mode != NFLBM_BATCH_LAUNCH && mode != NFLBM_BATCH_GRAPH && mode != NFLBM_BATCH_PER_SIM)
     return bfail(b, NFLBM_EINVAL, "unknown batch mode");
-  hipEvent_t e0, e1;
-  BHIPCHK(b, hipEventCreate(&e0));
-  BHIPCHK(b, hipEventCreate(&e1));
-  BHIPCHK(b, hipEventRecord(e0, b->stream));
-  int rc = batch_run(b, nsteps, mode);
-  if (rc == NFLBM_OK) {
-    BHIPCHK(b, hipEventRecord(e1, b->stream));
-    BHIPCHK(b, hipEventSynchronize(e1));
-    float t = 0.f;
-    BHIPCHK(b, hipEventElapsedTime(&t, e0, e1));
-    *ms = t;
-    BHIPCHK(b, nan_poll(&b->nan_pending, &b->nan_seen, b->nan_host, b->nan_ev, true));
-    if (b->nan_seen) rc = bfail(b, NFLBM_ENUMERIC, "a NaN or Inf appeared in a member's state");
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  return rc;
+  return batch_timed(b, nsteps, mode, ms, true);
 }
 
 int nflbm_batch_set_launch(nflbm_batch* b, int tx_log2, int graph_steps) {
@@ -2892,8 +2898,8 @@ int nflbm_batch_autotune(nflbm_batch* b, const char* cache_path) {
     if (!batch_tile_fits(b, l)) continue;
     rc = nflbm_batch_set_launch(b, l, 0);
     double ms = 0.0;
-    if (rc == NFLBM_OK) rc = batch_run(b, b->graph_steps, NFLBM_BATCH_GRAPH);  // warm-up and capture
-    if (rc == NFLBM_OK) rc = nflbm_batch_step_timed(b, K, NFLBM_BATCH_GRAPH, &ms);
+    if (rc == NFLBM_OK) rc = batch_run(b, b->graph_steps, NFLBM_BATCH_GRAPH, false);  // warm-up and capture
+    if (rc == NFLBM_OK) rc = batch_timed(b, K, NFLBM_BATCH_GRAPH, &ms, false);
     if (rc == NFLBM_OK && ms < best_ms) {
       best_ms = ms;
       best = {l};

@@ -166,11 +166,32 @@ static void other_record_set() {
   nflbm_batch_destroy(b);
 }
 
+// The batch autotuner chooses the tile width of the two kernels, so it times
+// those and not the fused launches, which have tiles of their own.
+static void batch_autotune_times_its_kernels() {
+  Problem p(NFLBM_D2Q9, 128, 96, 1, 3, NFLBM_FP32);
+  nflbm_batch* b = nullptr;
+  CHECK(nflbm_batch_create(&p.cfg, 1, &b) == NFLBM_OK);
+  std::vector<double> C(3 * 128 * 96, 1.0 / 3.0);
+  CHECK(nflbm_batch_set_fields(b, 0, C.data(), nullptr, nullptr) == NFLBM_OK);
+  CHECK(nflbm_batch_step(b, 3, NFLBM_BATCH_GRAPH) == NFLBM_OK);
+  CHECK(state().count("fused2d_batch") > 0);
+  state().launches.clear();
+  CHECK(nflbm_batch_autotune(b, nullptr) == NFLBM_OK);
+  CHECK(state().count("fused2d_batch") == 0);
+  CHECK(state().count("batch") > 0 && state().count("graph") > 0);
+  state().launches.clear();
+  CHECK(nflbm_batch_step(b, 4, NFLBM_BATCH_GRAPH) == NFLBM_OK);
+  CHECK(state().count("fused2d_batch") > 0);
+  nflbm_batch_destroy(b);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
   else if (name == "state_parity") state_parity();
   else if (name == "stepping_allocates_nothing") stepping_allocates_nothing();
+  else if (name == "batch_autotune_times_its_kernels") batch_autotune_times_its_kernels();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

@@ -12,7 +12,8 @@ CSRC = os.path.join(ROOT, "paper_2605_22214_amd", "csrc")
 HOST = os.path.join(ROOT, "tests", "host")
 CLANG = "/opt/rocm/llvm/bin/clang++"
 
-CHECKS = ["restored_velocities", "state_parity", "stepping_allocates_nothing", "other_record_set"]
+CHECKS = ["restored_velocities", "state_parity", "stepping_allocates_nothing", "other_record_set",
+          "batch_autotune_times_its_kernels"]
 
 
 @pytest.fixture(scope="module")
