@@ -2662,7 +2662,7 @@ int nflbm_autotune(nflbm_sim* sim, const char* cache_path) {
     for (const auto& c : cands) {
       const bool ok = pass == 0 ? apply_launch(sim, c.first, c.second) : apply_conc_launch(sim, c.first, c.second);
       if (!ok) continue;
-      rc = nflbm_step(sim, 2);
+      for (int warm = 0; warm < 2 && rc == NFLBM_OK; ++warm) rc = nflbm_step(sim, 1);   // two kernels, not fused
       double ms = 0.0, mu = 0.0;
       if (rc == NFLBM_OK) rc = nflbm_step_timed(sim, K, &ms, &mu);
       if (rc != NFLBM_OK) break;

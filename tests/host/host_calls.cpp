@@ -186,12 +186,28 @@ static void batch_autotune_times_its_kernels() {
   nflbm_batch_destroy(b);
 }
 
+// So does a simulation's own, its warm-up steps included: they load the
+// kernels of the shape that the timed steps take.
+static void autotune_warms_its_kernels() {
+  for (int flags : {0, int(NFLBM_FLAG_NO_HYDRO), NFLBM_FLAG_NO_HYDRO | NFLBM_FLAG_C2C2_MOBILITY}) {
+    Problem p(NFLBM_D2Q9, 128, 96, 1, 3, NFLBM_FP32, flags);
+    nflbm_sim* s = make(p);
+    CHECK(nflbm_step(s, 1) == NFLBM_OK);
+    state().launches.clear();
+    CHECK(nflbm_autotune(s, nullptr) == NFLBM_OK);
+    CHECK(state().count("fused2d") + state().count("fused_mob") == 0);
+    CHECK(state().count("update") > 0);
+    nflbm_destroy(s);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
   else if (name == "state_parity") state_parity();
   else if (name == "stepping_allocates_nothing") stepping_allocates_nothing();
   else if (name == "batch_autotune_times_its_kernels") batch_autotune_times_its_kernels();
+  else if (name == "autotune_warms_its_kernels") autotune_warms_its_kernels();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());
