@@ -276,14 +276,12 @@ void free_device(nflbm_sim* s) {
   s->lam = nullptr;
   s->spec = nullptr;
   s->spart = nullptr;
-  if (s->stage) {
-    (void)hipHostFree(s->stage);
-    for (hipEvent_t& e : s->stage_ev) {
-      if (e) (void)hipEventDestroy(e);
-      e = nullptr;
-    }
-  }
+  if (s->stage) (void)hipHostFree(s->stage);
   s->stage = nullptr;
+  for (hipEvent_t& e : s->stage_ev) {      // made before the slots
+    if (e) (void)hipEventDestroy(e);
+    e = nullptr;
+  }
   if (s->other) (void)hipFree(s->other);
   s->other = nullptr;
   if (s->fields) (void)hipFree(s->fields);
@@ -966,7 +964,6 @@ void fill_faces(const nflbm_sim& s, FaceBC<T>* p) {
   }
 }
 
-// Reconstruct C and evaluate the node fields of the current state.
 // The staging memory and its events; false where they cannot be had.
 bool ensure_stage(nflbm_sim* s) {
   if (s->stage) return true;
@@ -1064,6 +1061,7 @@ hipError_t copy_out(nflbm_sim* s, void* dst, const void* src, size_t bytes) {
   return e;
 }
 
+// Reconstruct C and evaluate the node fields of the current state.
 int compute_fields(nflbm_sim* s) {
   int rc = ensure_fields(s);
   if (rc) return rc;

@@ -1,5 +1,6 @@
 // Checks of the library's host code over the fake runtime of fake_hip.h, one
 // a run: host_calls NAME.  Exit status 0 when the check holds.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -201,6 +202,22 @@ static void autotune_warms_its_kernels() {
   }
 }
 
+// A large read-back without pinned memory for its slots copies plainly and
+// gives back the events it made for them.
+static void readback_without_pinned_memory() {
+  Problem p(NFLBM_D3Q19, 128, 128, 86, 3, NFLBM_FP32);
+  nflbm_sim* s = make(p);
+  std::vector<double> out(3 * size_t(128 * 128 * 86));
+  state().pinned_fails = true;
+  for (int i = 0; i < 2; ++i) {
+    std::fill(out.begin(), out.end(), -1.0);
+    CHECK(nflbm_get_field(s, NFLBM_FIELD_C, out.data()) == NFLBM_OK);
+    for (size_t q = 0; q < out.size(); ++q) CHECK(out[q] == double(q));
+  }
+  nflbm_destroy(s);
+  CHECK(state().device.empty() && state().pinned.empty() && state().events == 0);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -208,6 +225,7 @@ int main(int argc, char** argv) {
   else if (name == "stepping_allocates_nothing") stepping_allocates_nothing();
   else if (name == "batch_autotune_times_its_kernels") batch_autotune_times_its_kernels();
   else if (name == "autotune_warms_its_kernels") autotune_warms_its_kernels();
+  else if (name == "readback_without_pinned_memory") readback_without_pinned_memory();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

@@ -13,7 +13,8 @@ HOST = os.path.join(ROOT, "tests", "host")
 CLANG = "/opt/rocm/llvm/bin/clang++"
 
 CHECKS = ["restored_velocities", "state_parity", "stepping_allocates_nothing", "other_record_set",
-          "batch_autotune_times_its_kernels", "autotune_warms_its_kernels"]
+          "batch_autotune_times_its_kernels", "autotune_warms_its_kernels",
+          "readback_without_pinned_memory"]
 
 
 @pytest.fixture(scope="module")
