@@ -131,7 +131,8 @@ struct nflbm_sim {
   double* fields = nullptr;
   double* red = nullptr;
   // read-back of large fields: pinned slots the device copies into and the
-  // event behind each slot's copy (made on first use)
+  // event behind each slot's copy (made on first use), for one call at a time
+  std::mutex stage_mx;
   unsigned char* stage = nullptr;
   hipEvent_t stage_ev[kStageSlots] = {};
   int cur = 0;
@@ -994,7 +995,9 @@ hipError_t copy_out(nflbm_sim* s, void* dst, const void* src, size_t bytes) {
     const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s->stream);
     return e != hipSuccess ? e : hipStreamSynchronize(s->stream);
   };
-  if (bytes < kStageMin || !ensure_stage(s)) return plain();
+  if (bytes < kStageMin) return plain();
+  std::lock_guard<std::mutex> slots(s->stage_mx);      // threads that read one simulation take turns
+  if (!ensure_stage(s)) return plain();
   const size_t n = (bytes + kStageBytes - 1) / kStageBytes;
   std::mutex mx;
   std::condition_variable filled, emptied;

@@ -4,6 +4,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "fake_hip.h"
@@ -218,6 +219,32 @@ static void readback_without_pinned_memory() {
   CHECK(state().device.empty() && state().pinned.empty() && state().events == 0);
 }
 
+// Two threads that read fields of one simulation each get their own whole.
+static void readback_from_two_threads() {
+  const size_t n = 128 * 128 * 86;
+  Problem p(NFLBM_D3Q19, 128, 128, 86, 3, NFLBM_FP32);
+  nflbm_sim* s = make(p);
+  std::vector<double> first(3 * n);
+  CHECK(nflbm_get_field(s, NFLBM_FIELD_P, first.data()) == NFLBM_OK);
+  std::vector<long long> wrong(2, 0);
+  auto read = [&](int t) {
+    const int field = t ? NFLBM_FIELD_V : NFLBM_FIELD_C;      // rows 3.. and 0.. of the fields
+    const size_t off = t ? 3 * n : 0;
+    std::vector<double> out(3 * n);
+    for (int i = 0; i < 8; ++i) {
+      std::fill(out.begin(), out.end(), -1.0);
+      if (nflbm_get_field(s, field, out.data()) != NFLBM_OK) ++wrong[t];
+      for (size_t q = 0; q < out.size(); ++q) wrong[t] += out[q] != double(off + q);
+    }
+  };
+  std::thread a(read, 0), b(read, 1);
+  a.join();
+  b.join();
+  CHECK(wrong[0] == 0 && wrong[1] == 0);
+  nflbm_destroy(s);
+  CHECK(state().device.empty() && state().pinned.empty() && state().events == 0);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -226,6 +253,7 @@ int main(int argc, char** argv) {
   else if (name == "batch_autotune_times_its_kernels") batch_autotune_times_its_kernels();
   else if (name == "autotune_warms_its_kernels") autotune_warms_its_kernels();
   else if (name == "readback_without_pinned_memory") readback_without_pinned_memory();
+  else if (name == "readback_from_two_threads") readback_from_two_threads();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

@@ -35,3 +35,26 @@ def test_large_fields_read_back_whole(shape):
     for C, got in zip(fields, out):
         assert np.array_equal(got[:2], C[:2])
         assert np.array_equal(got[2], 1.0 - (C[0] + C[1]))
+
+
+def test_two_threads_read_one_simulation():
+    shape = (128, 128, 86)
+    s = nf.Simulation("D3Q19", shape, 0.01 * (np.ones((3, 3)) - np.eye(3)), np.ones(3), m=0.05)
+    C = np.random.default_rng(2).uniform(0.1, 0.4, size=(3,) + shape[::-1])
+    C[2] = 1.0 - C[0] - C[1]
+    s.set_fields(C)
+    s.step(2)
+    want = {name: s.get_field(name) for name in ("C", "F")}
+    got = {"C": [], "F": []}
+
+    def read(name):
+        for _ in range(4):
+            got[name].append(s.get_field(name))
+
+    threads = [threading.Thread(target=read, args=(name,)) for name in got]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for name in got:
+        assert all(np.array_equal(v, want[name]) for v in got[name])
