@@ -281,7 +281,9 @@ int nflbm_set_outflow(nflbm_sim *sim, int face);
  * value.  Solid nodes hold no fluid: their concentrations and every field
  * read back as 0, and diagnostics leave them out.  Call before
  * nflbm_set_fields (which fills only the fluid nodes); NULL removes the
- * geometry.  Takes 4 bytes per node of device memory besides the state.
+ * geometry.  Takes 4 bytes per node of device memory besides the state, and 4
+ * more while a face is open or the outflow's (ENOMEM, here and from
+ * nflbm_set_open_face and nflbm_set_outflow, where they do not fit).
  * Goes with open faces and the outflow face as those describe (ENOTSUP for a
  * mask the outflow face cannot take), and with batch members (the batch
  * picks the change up at its next step).  EINVAL if every node is solid.

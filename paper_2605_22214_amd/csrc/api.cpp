@@ -102,9 +102,10 @@ struct nflbm_sim {
   void* out_buf = nullptr;
   double* out_red = nullptr;
   int out_blocks = 0;
-  // solid geometry: per-node pull masks (StepArgs::bb), behind them the entering
-  // directions across open faces (StepArgs::ob), and the caller's mask
+  // solid geometry: per-node pull masks (StepArgs::bb), while a face is open or
+  // the outflow's the entering directions (StepArgs::ob), and the caller's mask
   uint32_t* bb = nullptr;
+  uint32_t* ob = nullptr;
   std::vector<unsigned char> solid_host;
   // concentration-dependent mobility: MobParams and the potential scratch
   bool c2c2 = false;
@@ -259,7 +260,8 @@ void free_device(nflbm_sim* s) {
   }
   if (s->params) (void)hipFree(s->params);
   if (s->bb) (void)hipFree(s->bb);
-  s->bb = nullptr;
+  if (s->ob) (void)hipFree(s->ob);
+  s->bb = s->ob = nullptr;
   if (s->faces) (void)hipFree(s->faces);
   s->faces = nullptr;
   if (s->out_buf) (void)hipFree(s->out_buf);
@@ -480,7 +482,7 @@ StepArgs make_args(const nflbm_sim* s, int src) {
   a.params = s->params;
   a.bb = s->bb;
   a.faces = s->faces;
-  a.ob = s->bb ? s->bb + s->n : nullptr;
+  a.ob = s->ob;
   a.out_face = s->out_face;
   if (s->out_face >= 0) {
     const size_t P = s->out_plane;
@@ -1705,12 +1707,26 @@ std::vector<std::pair<void**, size_t>> state_arrays(nflbm_sim* s) {
   return v;
 }
 
+// Memory for a map of n words at *p, where there is none yet.
+int ensure_map(nflbm_sim* sim, uint32_t** p) {
+  if (*p || hipMalloc(reinterpret_cast<void**>(p), sim->n * sizeof(uint32_t)) == hipSuccess) return NFLBM_OK;
+  *p = nullptr;
+  return fail(sim, NFLBM_ENOMEM, "cannot allocate the solid geometry");
+}
+
 // The map of entering directions for the walls, solid nodes and open faces
-// as they are now; without solid nodes the kernels form it from the faces.
+// as they are now, freed when no face is open; without solid nodes the kernels
+// form it from the faces.
 int build_open_map(nflbm_sim* sim) {
   const int open = sim->open_mask | (sim->out_face >= 0 ? 1 << sim->out_face : 0);
-  if (!open || !sim->bb) return NFLBM_OK;
-  HIPCHK(sim, launch_build_ob(sim->lat, open, sim->bb + sim->n, make_args(sim, sim->cur), sim->stream));
+  if (!open || !sim->bb) {
+    if (sim->ob) (void)hipFree(sim->ob);
+    sim->ob = nullptr;
+    return NFLBM_OK;
+  }
+  const int rc = ensure_map(sim, &sim->ob);
+  if (rc) return rc;
+  HIPCHK(sim, launch_build_ob(sim->lat, open, sim->ob, make_args(sim, sim->cur), sim->stream));
   HIPCHK(sim, hipStreamSynchronize(sim->stream));
   return NFLBM_OK;
 }
@@ -1982,6 +1998,10 @@ int nflbm_set_open_face(nflbm_sim* sim, int face, const double* v_b, const doubl
       sum += C_b[i];
     }
     if (std::fabs(sum - 1.0) > 1e-12) return fail(sim, NFLBM_EINVAL, "C_b must sum to 1");
+    if (sim->bb) {
+      const int rc = ensure_map(sim, &sim->ob);
+      if (rc) return rc;
+    }
     for (int d = 0; d < 3; ++d) sim->face_v[face][d] = v_b[d];
     for (int i = 0; i < sim->N; ++i) sim->face_c[face][i] = C_b[i];
     sim->open_mask |= 1 << face;
@@ -2019,6 +2039,10 @@ int nflbm_set_outflow(nflbm_sim* sim, int face) {
   }
   if (sim->out_face >= 0 && sim->out_face != face) {
     const int rc = nflbm_set_outflow(sim, -1);
+    if (rc) return rc;
+  }
+  if (sim->bb) {
+    const int rc = ensure_map(sim, &sim->ob);
     if (rc) return rc;
   }
   const int ax = face / 2;
@@ -2067,7 +2091,8 @@ int nflbm_set_solid(nflbm_sim* sim, const unsigned char* solid) {
   }
   if (!solid) {
     if (sim->bb) (void)hipFree(sim->bb);
-    sim->bb = nullptr;
+    if (sim->ob) (void)hipFree(sim->ob);
+    sim->bb = sim->ob = nullptr;
     sim->solid_host.clear();
     sim->out_fluid = fluid_out;
     if (!sim->shape_chosen) (void)default_launch(sim);
@@ -2078,13 +2103,19 @@ int nflbm_set_solid(nflbm_sim* sim, const unsigned char* solid) {
   size_t fluid = 0;
   for (size_t q = 0; q < n; ++q) fluid += solid[q] ? 0 : 1;
   if (fluid == 0) return fail(sim, NFLBM_EINVAL, "every node is solid");
-  if (!sim->bb && hipMalloc(reinterpret_cast<void**>(&sim->bb), 2 * n * sizeof(uint32_t)) != hipSuccess) {
-    sim->bb = nullptr;
-    return fail(sim, NFLBM_ENOMEM, "cannot allocate the solid geometry");
-  }
+  // all memory first: a call without room for it changes nothing
   unsigned char* dmask = nullptr;
   if (hipMalloc(reinterpret_cast<void**>(&dmask), n) != hipSuccess)
     return fail(sim, NFLBM_ENOMEM, "cannot allocate the solid mask");
+  const bool first = !sim->bb;
+  int mrc = ensure_map(sim, &sim->bb);
+  if (mrc == NFLBM_OK && (sim->open_mask || sim->out_face >= 0)) mrc = ensure_map(sim, &sim->ob);
+  if (mrc != NFLBM_OK) {
+    (void)hipFree(dmask);
+    if (first && sim->bb) (void)hipFree(sim->bb);
+    if (first) sim->bb = nullptr;
+    return mrc;
+  }
   hipError_t e = hipMemcpyAsync(dmask, solid, n, hipMemcpyHostToDevice, sim->stream);
   if (e == hipSuccess) e = launch_build_bb(sim->lat, dmask, sim->bb, make_args(sim, sim->cur), sim->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sim->stream);

@@ -245,6 +245,50 @@ static void readback_from_two_threads() {
   CHECK(state().device.empty() && state().pinned.empty() && state().events == 0);
 }
 
+// Solid nodes take 4 bytes a node, 8 while a face is open or the outflow's;
+// where the second map does not fit, nothing changes.
+static void solid_memory() {
+  Problem p(NFLBM_D3Q19, 32, 24, 20, 3, NFLBM_FP32);
+  p.cfg.wall[0] = 1;
+  const size_t n = 32 * 24 * 20;
+  nflbm_sim* s = make(p);
+  std::vector<unsigned char> solid(n, 0);
+  for (size_t q = 0; q < n; ++q) solid[q] = (q / 32) % 24 < 3;
+  const double v[3] = {0.01, 0.0, 0.0}, c[3] = {0.5, 0.25, 0.25};
+  const size_t base = state().device_bytes();
+  CHECK(nflbm_set_solid(s, solid.data()) == NFLBM_OK);
+  CHECK(state().device_bytes() == base + 4 * n);
+  state().fail_at = 4 * n;
+  CHECK(nflbm_set_open_face(s, 0, v, c) == NFLBM_ENOMEM);
+  CHECK(nflbm_set_outflow(s, 1) == NFLBM_ENOMEM);
+  CHECK(nflbm_set_solid(s, nullptr) == NFLBM_OK);
+  CHECK(nflbm_set_solid(s, solid.data()) == NFLBM_ENOMEM);
+  CHECK(state().device_bytes() == base);
+  CHECK(nflbm_step(s, 1) == NFLBM_OK);
+  CHECK(!state().launches.back().step.bb && !state().launches.back().step.faces);
+  state().fail_at = 0;
+  CHECK(nflbm_set_open_face(s, 0, v, c) == NFLBM_OK);
+  const size_t open = state().device_bytes();
+  CHECK(open < base + 4 * n);
+  CHECK(nflbm_set_solid(s, solid.data()) == NFLBM_OK);
+  CHECK(state().device_bytes() == open + 8 * n && state().count("build_ob") == 1);
+  CHECK(nflbm_set_outflow(s, 1) == NFLBM_OK && state().count("build_ob") == 2);
+  CHECK(nflbm_step(s, 1) == NFLBM_OK);
+  // the outflow moves to the other face
+  CHECK(nflbm_set_open_face(s, 0, nullptr, nullptr) == NFLBM_OK && nflbm_set_outflow(s, 0) == NFLBM_OK);
+  CHECK(nflbm_step(s, 1) == NFLBM_OK);
+  CHECK(nflbm_set_outflow(s, 1) == NFLBM_OK && nflbm_set_open_face(s, 0, v, c) == NFLBM_OK);
+  CHECK(nflbm_step(s, 1) == NFLBM_OK);
+  for (const fake::Launch& l : state().launches)
+    if (l.kind == "conc" && l.step.faces) CHECK(l.step.bb && l.step.ob);
+  CHECK(nflbm_set_outflow(s, -1) == NFLBM_OK && nflbm_set_open_face(s, 0, nullptr, nullptr) == NFLBM_OK);
+  CHECK(state().device_bytes() == base + 4 * n);
+  CHECK(nflbm_set_solid(s, nullptr) == NFLBM_OK);
+  CHECK(state().device_bytes() == base);
+  nflbm_destroy(s);
+  CHECK(state().device.empty() && state().pinned.empty() && state().events == 0);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -254,6 +298,7 @@ int main(int argc, char** argv) {
   else if (name == "autotune_warms_its_kernels") autotune_warms_its_kernels();
   else if (name == "readback_without_pinned_memory") readback_without_pinned_memory();
   else if (name == "readback_from_two_threads") readback_from_two_threads();
+  else if (name == "solid_memory") solid_memory();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());
