@@ -129,9 +129,9 @@ enum {
  * the reconstruction forms the moments sum_k f_k and sum_k e_k f_k of the
  * streamed populations from the neighbours' records (halfway bounce-back at
  * walls and solid nodes) and the update reads those.  This is the same
- * arithmetic as the population form up to rounding; FP64 and FP32 storage
- * only (FP16S keeps its binary16 populations), no open faces or outflow
- * (they need g as populations anyway).  NFLBM_FLAG_F_POPULATIONS keeps the
+ * arithmetic as the population form up to rounding, in every precision and
+ * with every boundary condition.  All members of a batch keep populations of f
+ * where one of them does.  NFLBM_FLAG_F_POPULATIONS keeps the
  * populations; nflbm_f_storage_form tells which form a simulation uses.  The
  * first step after nflbm_set_fields takes each node's f as the equilibrium
  * f^eq(P0, v0) of its own initial record, as the population form stores it. */

@@ -2757,13 +2757,18 @@ int nflbm_batch_create(const nflbm_config* cfgs, int count, nflbm_batch** out) {
       m->in_batch = true;
       b->members.push_back(m);
     }
-    bool same = true;
-    for (nflbm_sim* m : b->members) same = same && m->gform == b->members[0]->gform;
-    if (same) break;
-    // a member fell back to populations (its LDS window): all do
+    bool same = true, same_f = true;
+    for (nflbm_sim* m : b->members) {
+      same = same && m->gform == b->members[0]->gform;
+      same_f = same_f && m->fform == b->members[0]->fform;
+    }
+    if (same && same_f) break;
+    // a member fell back to populations of g (its LDS window), or keeps those
+    // of f (a relaxation time other than 1, or f not evolved): all do, as the
+    // batch's kernels read one form
     for (nflbm_sim* m : b->members) nflbm_destroy(m);
     b->members.clear();
-    for (auto& c : cc) c.flags |= NFLBM_FLAG_G_POPULATIONS;
+    for (auto& c : cc) c.flags |= same ? NFLBM_FLAG_F_POPULATIONS : NFLBM_FLAG_G_POPULATIONS;
   }
   for (nflbm_sim* m : b->members) {
     b->nodes += static_cast<long long>(m->n);

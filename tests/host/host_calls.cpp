@@ -289,6 +289,24 @@ static void solid_memory() {
   CHECK(state().device.empty() && state().pinned.empty() && state().events == 0);
 }
 
+// A batch launch takes one storage form of f for all members.
+static void batch_shares_the_form_of_f() {
+  Problem a(NFLBM_D2Q9, 64, 48, 1, 3, NFLBM_FP32), b(NFLBM_D2Q9, 40, 48, 1, 3, NFLBM_FP32),
+      c(NFLBM_D2Q9, 32, 32, 1, 3, NFLBM_FP32, NFLBM_FLAG_NO_HYDRO);
+  b.tau.assign(3, 0.8);
+  const std::vector<std::vector<nflbm_config>> mixes = {{a.cfg, b.cfg}, {b.cfg, a.cfg}, {a.cfg, c.cfg}, {c.cfg, a.cfg},
+                                                        {a.cfg, a.cfg}, {c.cfg, c.cfg}};
+  for (const auto& m : mixes) {
+    nflbm_batch* h = nullptr;
+    CHECK(nflbm_batch_create(m.data(), int(m.size()), &h) == NFLBM_OK);
+    const int form = nflbm_f_storage_form(nflbm_batch_member(h, 0));
+    for (int i = 0; i < nflbm_batch_count(h); ++i) CHECK(nflbm_f_storage_form(nflbm_batch_member(h, i)) == form);
+    CHECK(form == (&m == &mixes[4]));
+    CHECK(nflbm_batch_step(h, 9, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+    nflbm_batch_destroy(h);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -299,6 +317,7 @@ int main(int argc, char** argv) {
   else if (name == "readback_without_pinned_memory") readback_without_pinned_memory();
   else if (name == "readback_from_two_threads") readback_from_two_threads();
   else if (name == "solid_memory") solid_memory();
+  else if (name == "batch_shares_the_form_of_f") batch_shares_the_form_of_f();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

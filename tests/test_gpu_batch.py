@@ -221,3 +221,27 @@ def test_reconstruction_launch_shapes_agree():
         if ref is None:
             ref = st
         assert np.array_equal(st, ref), (tx, zc)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16s"])
+@pytest.mark.parametrize("lattice,shape", [("D2Q9", (41, 30, 1)), ("D3Q19", (18, 11, 9))])
+def test_members_of_both_forms_of_f(lattice, shape, precision):
+    """Members with and without unit relaxation times, and without the flow,
+    in one batch: all keep populations of f, as each does alone under the flag."""
+    N = 3
+    cfgs = [dict(lattice=lattice, shape=shape, sigma=0.01 * (np.ones((N, N)) - np.eye(N)), tau=np.full(N, tau),
+                 m=0.05, precision=precision, flags=flags, omega_stab=omega)
+            for tau, flags, omega in ((1.0, 0, 0.0), (0.8, 0, 0.05), (1.0, nf.FLAG_NO_HYDRO, 0.0))]
+    for order in ((0, 1, 2), (2, 0), (1, 0)):
+        batch = nf.Batch([cfgs[i] for i in order])
+        alone = [nf.Simulation(**dict(cfgs[i], flags=cfgs[i]["flags"] | nf.FLAG_F_POPULATIONS)) for i in order]
+        for i, s in enumerate(alone):
+            C = 1.0 / N + np.random.default_rng(i).uniform(-0.1, 0.1, size=(N,) + shape[::-1])
+            C /= C.sum(axis=0)
+            batch.set_fields(i, C)
+            s.set_fields(C)
+        batch.step(7, "launch")
+        for member, s in zip(batch.members, alone):
+            assert member.f_storage_form() == "populations"
+            s.step(7)
+            assert np.array_equal(member.get_state(), s.get_state())
