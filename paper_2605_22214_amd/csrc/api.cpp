@@ -648,7 +648,8 @@ void fused_tiling(const FusedPlan& p, int nx, int ny, int* w, int* h, int* tx, i
 }
 
 // The shape for the simulations m[0..count) stepped together (they share N,
-// precision and record form); false if none fits LDS.  A lattice that small
+// precision and record form); false if none fits LDS, or where the two kernels
+// are the faster.  A lattice that small
 // tiles cannot spread over the chip is bound by the latency of each launch and
 // phase: few nodes a workgroup and more steps a launch.  A lattice of several
 // rounds of workgroups is bound by the work, which larger tiles and two steps
@@ -659,36 +660,91 @@ void fused_tiling(const FusedPlan& p, int nx, int ny, int* w, int* h, int* tx, i
 // 24 x 8; N = 6 FP64 at 700 x 700, 48.7 us with 24 x 16 against 56.0 us.
 bool fused_plan(const nflbm_sim* const* m, size_t count, FusedPlan* out) {
   const nflbm_sim* s = m[0];
-  const bool wide = s->store == NFLBM_FP64 && s->N >= 5;   // over 128 VGPRs
-  const FusedPlan small = wide ? FusedPlan{5, 3, 4, 512} : FusedPlan{5, 4, 4, 1024};
-  FusedPlan large = wide ? FusedPlan{5, 2, 16, 512} : FusedPlan{5, 2, 24, 1024};
-  if (s->store != NFLBM_FP64 && s->N >= 4) large.threads = 512;
-  // N = 5 and 6 in FP64: all 24 rows in one pass a phase (12 wavefronts), at
-  // 168 VGPRs (28 spilled at N = 6), beat two passes at 204 (nine 300 x 150 lenses,
-  // N = 6: 43.5 -> 38.9 us a step); from N = 7 too many spill
-  if (wide && s->N <= 6) large.threads = 768;
-  if (!s->fform) large = FusedPlan{6, 2, 24, 1024};
-  const FusedPlan medium{5, 2, 8, 512};
-  const FusedPlan plans[] = {small, {5, 3, 8, 512}, medium, large, {5, 2, 16, 512}, medium};
-  for (int q = 0; q < 6; ++q) {
-    const FusedPlan& p = plans[q];
-    const size_t lds = fused_lds(s, p);
-    if (lds > s->lds_max) continue;
-    long long tiles = 0;
+  const int N = s->N;
+  const bool f64 = s->store == NFLBM_FP64;
+  const bool wide = f64 && N >= 5;   // over 128 VGPRs
+  auto tiles = [&](const FusedPlan& p) {
+    long long c = 0;
     for (size_t i = 0; i < count; ++i) {
       int w, h, tx, ty;
       fused_tiling(p, m[i]->nx, m[i]->ny, &w, &h, &tx, &ty);
-      tiles += 1LL * tx * ty;
+      c += 1LL * tx * ty;
     }
-    // one round of workgroups: one a CU (256 CUs), the medium ones two where
-    // LDS holds them; the last three are for lattices beyond that
-    const long long round = q < 2 ? 256 : (2 * lds <= s->lds_max ? 512 : 256);
-    if (q >= 3 || tiles <= round) {
-      *out = p;
-      return true;
-    }
+    return c;
+  };
+  auto take = [&](const FusedPlan& p) {
+    *out = p;
+    return true;
+  };
+  auto fits = [&](const FusedPlan& p, size_t groups) { return groups * fused_lds(s, p) <= s->lds_max; };
+  // one round of workgroups: one a CU (256 CUs), medium tiles two where LDS
+  // holds them
+  const FusedPlan small = wide ? FusedPlan{5, 3, 4, 512} : FusedPlan{5, 4, 4, 1024};
+  const FusedPlan medium{5, 2, 8, 512};
+  for (const FusedPlan& p : {small, FusedPlan{5, 3, 8, 512}})
+    if (fits(p, 1) && tiles(p) <= 256) return take(p);
+  if (fits(medium, 1) && tiles(medium) <= (fits(medium, 2) ? 512 : 256)) return take(medium);
+  if (!s->fform) {
+    for (const FusedPlan& p : {FusedPlan{6, 2, 24, 1024}, FusedPlan{5, 2, 16, 512}, medium})
+      if (fits(p, 1)) return take(p);
+    return false;
   }
-  return false;
+  // Beyond one round, with the flow.  options: the stabilising term or the
+  // potential force, whose arithmetic the halo repeats as well.
+  bool options = false;
+  for (size_t i = 0; i < count; ++i) options = options || (m[i]->step_flags & (kFlagOmega | kFlagPotential));
+  if (f64 ? N <= 4 : N <= 3) return take({5, 2, 24, 1024});
+  // From there on tiles as tall as LDS holds, in float twice a CU: one float
+  // workgroup of 512 threads a CU leaves its SIMDs two wavefronts each (N = 5
+  // at 700 x 650, FP16S: tiles of 24 x 24 22.4 us, of 24 x 20 14.8 us, the two
+  // kernels 15.5 us).  In FP64 once a CU, on 768 threads in N = 5 and 6, all
+  // rows in one pass a phase; with the options N = 6 spills too much for that
+  // (700 x 650: 52.5 us on 512 threads, 63.5 on 768, two kernels 58.1).
+  const bool half = s->store == NFLBM_FP16S;
+  auto tallest = [&](FusedPlan p, size_t groups) {
+    while (p.h > 8 && !fits(p, groups)) p.h -= 4;
+    return p;
+  };
+  // Beyond one round the two kernels are faster where registers or LDS keep a
+  // second workgroup off the CU, or the options weigh most (us a step at 1000 x
+  // 1010, two kernels against the best fused shape): in float N = 8 (FP32 71
+  // against 71 to 83, with the options 89 against 106), N = 7 in FP16S (52, 54)
+  // and, with the options, in FP32 (at 1500 x 1450 128, 130), N = 5 with them in
+  // FP16S (40, 38, but at 560 x 540 12, 14.6).  One round of the tallest tile
+  // still pays there (370 x 370 FP16S N = 7: 13.4, 10.8), at N = 8 without the
+  // options.
+  if (!f64 && (N == 8 || (N == 7 && (half || options)) || (N == 5 && half && options))) {
+    const FusedPlan p = tallest({5, 2, 24, 512}, 1);
+    return (N < 8 || !options) && fits(p, 1) && tiles(p) <= 256 && take(p);
+  }
+  const size_t groups = f64 ? 1 : 2;
+  FusedPlan p = tallest({5, 2, 24, f64 && (N == 5 || (N == 6 && !options)) ? 768 : 512}, groups);
+  if (!fits(p, groups)) return false;
+  const long long slots = 256LL * static_cast<long long>(groups);
+  auto rounds = [&](const FusedPlan& q) { return (tiles(q) + slots - 1) / slots; };
+  const long long full = rounds(p);
+  // With the options, N = 7 in FP64 and N = 6 in FP16S gain only in the first
+  // rounds (FP64 560 x 540 56 us by two kernels, 52 fused, 1000 x 1010 123, 143;
+  // FP16S 600 x 580 0.92 of the two kernels' time, 1500 x 1450 1.06).
+  if (options && ((f64 && N == 7 && full > 6) || (half && N == 6 && full > 4))) return false;
+  // A second round of few workgroups costs a whole one (560 x 540 FP32 N = 5:
+  // 1.27 rounds 12.2 us, two kernels 11.9; FP64 N = 8 with the options, 290 x
+  // 280: 1.22 rounds 1.15 of the two kernels' time).
+  if (full == 2 && (f64 ? N >= 7 && options : N >= 5)) {
+    const long long tenths = f64 && N == 7 ? 15 : 13;
+    if (10 * tiles(p) < tenths * slots) return false;
+  }
+  // In the first rounds the shortest tile that takes no more of them: 420 x 430
+  // FP32 N = 4, one round, 7.5 us with tiles of 24 x 24, 6.2 with 24 x 16; 530 x
+  // 520 FP64 N = 5, three, 24.2 us with 24 x 20, 22.9 with 24 x 16.  (With two
+  // workgroups a CU a third round already overlaps the others: 800 x 830 FP16S
+  // N = 4 0.92 of the two kernels' time with 24 x 24, 0.96 with 24 x 20.)
+  for (FusedPlan q = p; full <= (f64 ? 3 : 2) && q.h > 8;) {
+    q.h -= 4;
+    if (rounds(q) > full) break;
+    p = q;
+  }
+  return take(p);
 }
 
 // Whether the configuration can take fused steps at all (node records of a

@@ -307,6 +307,51 @@ static void batch_shares_the_form_of_f() {
   }
 }
 
+// The shape and number of the workgroups of four steps of an nx x ny lattice
+// (threads 0 where the two kernels take them).
+static fake::Launch four_steps(int nx, int ny, int N, int precision, double omega, int flags = 0) {
+  Problem p(NFLBM_D2Q9, nx, ny, 1, N, precision, flags);
+  p.cfg.omega_stab = omega;
+  nflbm_sim* s = make(p);
+  CHECK(nflbm_step(s, 1) == NFLBM_OK);
+  state().launches.clear();
+  CHECK(nflbm_step(s, 4) == NFLBM_OK);
+  const fake::Launch l = state().launches.back();
+  nflbm_destroy(s);
+  return l;
+}
+
+// Beyond one round of workgroups the fused steps are taken where they measured
+// faster than the two kernels.
+static void fused_shapes() {
+  const size_t lds = 160 << 10;
+  for (int precision : {NFLBM_FP64, NFLBM_FP32, NFLBM_FP16S})
+    for (int N = 2; N <= 8; ++N)
+      for (double omega : {0.0, 0.05})
+        for (int flags : {0, int(NFLBM_FLAG_NO_HYDRO)}) {
+          const bool f64 = precision == NFLBM_FP64, half = precision == NFLBM_FP16S, options = omega != 0.0;
+          const fake::Launch big = four_steps(1100, 1000, N, precision, omega, flags);
+          const bool two = !flags && (f64 ? N == 7 && options
+                                          : N == 8 || (N == 7 && (half || options)) || (half && (N == 5 || N == 6) && options));
+          CHECK((big.kind == "fused2d") == !two);
+          if (two) continue;
+          CHECK(big.shape.lds <= lds);
+          if (!f64 && N >= 4 && !flags) CHECK(big.shape.threads == 512 && 2 * big.shape.lds <= lds);
+          if (f64 && N >= 7 && !flags) CHECK(big.fused.tile_h >= 11);
+          // a small lattice is one round of small tiles in every form
+          const fake::Launch small = four_steps(90, 70, N, precision, omega, flags);
+          CHECK(small.kind == "fused2d" && small.shape.blocks <= 256);
+        }
+  // a second round of few workgroups
+  CHECK(four_steps(560, 540, 5, NFLBM_FP32, 0.0).kind != "fused2d");
+  CHECK(four_steps(700, 650, 5, NFLBM_FP32, 0.0).kind == "fused2d");
+  // the shortest tile of one round
+  CHECK(four_steps(420, 430, 4, NFLBM_FP32, 0.0).fused.tile_h <= 16);
+  // N = 7 in FP16S: one round of tall tiles, then the two kernels
+  CHECK(four_steps(370, 370, 7, NFLBM_FP16S, 0.0).kind == "fused2d");
+  CHECK(four_steps(420, 430, 7, NFLBM_FP16S, 0.0).kind != "fused2d");
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -318,6 +363,7 @@ int main(int argc, char** argv) {
   else if (name == "readback_from_two_threads") readback_from_two_threads();
   else if (name == "solid_memory") solid_memory();
   else if (name == "batch_shares_the_form_of_f") batch_shares_the_form_of_f();
+  else if (name == "fused_shapes") fused_shapes();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

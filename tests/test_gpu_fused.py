@@ -250,3 +250,28 @@ def _resting_bytes(cfg, N, case):
         a.step(1)
     b.step(9)
     assert np.array_equal(a.get_state(), b.get_state()), case
+
+
+@pytest.mark.parametrize("shape,N,precision,flags,omega", [
+    ((701, 643), 5, "fp32", PLAIN, 0.0),      # 24 x 20, two workgroups a CU
+    ((611, 470), 5, "fp16s", PLAIN, 0.0),
+    ((601, 580), 6, "fp32", POT, 0.05),       # 24 x 16
+    ((563, 541), 7, "fp32", PLAIN, 0.0),      # 24 x 12
+    ((371, 370), 8, "fp16s", PLAIN, 0.0),     # one round of the tallest tile
+    ((561, 540), 5, "fp64", PLAIN, 0.0),      # 24 x 20, 768 threads
+    ((333, 299), 6, "fp64", PLAIN, 0.05),     # 24 x 16, 512 threads
+    ((431, 419), 7, "fp64", PLAIN, 0.0),      # 24 x 12
+    ((431, 419), 8, "fp64", POT, 0.05),
+    ((1001, 523), 8, "fp32", PLAIN, 0.05),    # the two kernels
+])
+def test_shapes_beyond_one_round(shape, N, precision, flags, omega):
+    cfg = _config(shape, N, precision, flags, omega, (1e-6, 0.0, 0.0))
+    a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+    C = _noise(shape, N, 7)
+    for s in (a, b):
+        s.set_fields(C)
+    for _ in range(8):
+        a.step(1)
+    b.step(3)
+    b.step(5)
+    _same(a, b)
