@@ -829,9 +829,14 @@ bool fused_mob_now(const nflbm_sim* s) {
 }
 
 // Two steps a launch where LDS holds their tiles, which halves what a launch
-// costs for a halo of five nodes instead of two.
+// costs for a halo of five nodes instead of two.  N = 8 in FP64 takes one: by
+// tiles of 8 rows while they are one round of workgroups (60 x 60: 17.1 us a
+// step, of 12 rows 19.0), then by as many rows as LDS holds, whose 16 with the
+// halo are one pass of the workgroup (480 x 480 with the stabilising term 292 ->
+// 202 us, the four launches of the general path 257).
 bool fused_mob_plan(const nflbm_sim* s, FusedPlan* p, size_t* lds) {
-  const FusedPlan plans[] = {{5, 2, 14, 512}, {5, 1, 16, 512}, {5, 1, 8, 512}, {5, 1, 4, 512}};
+  const bool one_round = 1LL * ((s->nx + 27) / 28) * ((s->ny + 7) / 8) <= 256;
+  const FusedPlan plans[] = {{5, 2, 14, 512}, {5, 1, 16, 512}, {5, 1, one_round ? 8 : 12, 512}, {5, 1, 8, 512}};
   for (const FusedPlan& q : plans) {
     *lds = fused_mob_position_bytes(s->N, s->ts) * 32 * size_t(q.h + 2 * (3 * q.T - 1));
     if (*lds > s->lds_max) continue;

@@ -152,9 +152,10 @@ hipError_t record_fused(const FusedLaunch& f) {
   state().launches.push_back(l);
   return hipSuccess;
 }
-hipError_t record_mob(int nsteps) {
+hipError_t record_mob(int blocks, int nsteps) {
   fake::Launch l{"fused_mob"};
   l.nsteps = nsteps;
+  l.shape.blocks = blocks;
   std::lock_guard<std::mutex> lk(fake::mx);
   state().launches.push_back(l);
   return hipSuccess;
@@ -195,14 +196,14 @@ hipError_t launch_mob_source(int, int, int, const MobArgs&, hipStream_t) { retur
 hipError_t launch_fused2d_0(int, const FusedLaunch& f, hipStream_t) { return record_fused(f); }
 hipError_t launch_fused2d_1(int, const FusedLaunch& f, hipStream_t) { return record_fused(f); }
 hipError_t launch_fused2d_2(int, const FusedLaunch& f, hipStream_t) { return record_fused(f); }
-hipError_t launch_fused_mob_0(int, const FusedMobArgs&, int, int n, uint32_t, size_t, hipStream_t) {
-  return record_mob(n);
+hipError_t launch_fused_mob_0(int, const FusedMobArgs&, int blocks, int n, uint32_t, size_t, hipStream_t) {
+  return record_mob(blocks, n);
 }
-hipError_t launch_fused_mob_1(int, const FusedMobArgs&, int, int n, uint32_t, size_t, hipStream_t) {
-  return record_mob(n);
+hipError_t launch_fused_mob_1(int, const FusedMobArgs&, int blocks, int n, uint32_t, size_t, hipStream_t) {
+  return record_mob(blocks, n);
 }
-hipError_t launch_fused_mob_2(int, const FusedMobArgs&, int, int n, uint32_t, size_t, hipStream_t) {
-  return record_mob(n);
+hipError_t launch_fused_mob_2(int, const FusedMobArgs&, int blocks, int n, uint32_t, size_t, hipStream_t) {
+  return record_mob(blocks, n);
 }
 
 }  // namespace nflbm

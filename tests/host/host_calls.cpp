@@ -352,6 +352,17 @@ static void fused_shapes() {
   CHECK(four_steps(420, 430, 7, NFLBM_FP16S, 0.0).kind != "fused2d");
 }
 
+// N = 8 in FP64 with the concentration-dependent mobility: one step a launch,
+// by tiles of 12 rows once those of 8 are more than a round of workgroups.
+static void mobility_shapes() {
+  const int flags = NFLBM_FLAG_NO_HYDRO | NFLBM_FLAG_C2C2_MOBILITY;
+  const fake::Launch small = four_steps(60, 64, 8, NFLBM_FP64, 0.05, flags);
+  CHECK(small.kind == "fused_mob" && small.nsteps == 1 && small.shape.blocks == 3 * 8);
+  const fake::Launch big = four_steps(480, 480, 8, NFLBM_FP64, 0.05, flags);
+  CHECK(big.kind == "fused_mob" && big.nsteps == 1 && big.shape.blocks == 18 * 40);
+  CHECK(four_steps(480, 480, 4, NFLBM_FP32, 0.05, flags).nsteps == 2);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -364,6 +375,7 @@ int main(int argc, char** argv) {
   else if (name == "solid_memory") solid_memory();
   else if (name == "batch_shares_the_form_of_f") batch_shares_the_form_of_f();
   else if (name == "fused_shapes") fused_shapes();
+  else if (name == "mobility_shapes") mobility_shapes();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

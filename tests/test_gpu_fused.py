@@ -275,3 +275,18 @@ def test_shapes_beyond_one_round(shape, N, precision, flags, omega):
     b.step(3)
     b.step(5)
     _same(a, b)
+
+
+def test_fused_mobility_tall_tiles():
+    shape, N = (311, 290), 8                # 28 x 12, one step a launch
+    cfg = _config(shape, N, "fp64", nf.FLAG_NO_HYDRO | nf.FLAG_C2C2_MOBILITY, 0.05)
+    cfg["m"] = 10.0
+    a, b = nf.Simulation(**cfg), nf.Simulation(**cfg)
+    C = _noise(shape, N, 8)
+    for s in (a, b):
+        s.set_fields(C)
+    for _ in range(5):
+        a.step(1)
+    b.step(2)
+    b.step(3)
+    assert np.array_equal(a.get_state(), b.get_state())

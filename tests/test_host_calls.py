@@ -15,7 +15,8 @@ CLANG = "/opt/rocm/llvm/bin/clang++"
 CHECKS = ["restored_velocities", "state_parity", "stepping_allocates_nothing", "other_record_set",
           "batch_autotune_times_its_kernels", "autotune_warms_its_kernels",
           "readback_without_pinned_memory", "readback_from_two_threads", "solid_memory",
-          "batch_shares_the_form_of_f", "fused_shapes"]
+          "batch_shares_the_form_of_f", "fused_shapes",
+          "mobility_shapes"]
 
 
 @pytest.fixture(scope="module")
