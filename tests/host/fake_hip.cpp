@@ -116,10 +116,6 @@ hipError_t hipStreamCreate(hipStream_t* s) {
   return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
-  *st = state().capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
-  return hipSuccess;
-}
 hipError_t hipStreamSynchronize(hipStream_t) {
   ++state().syncs;
   return hipSuccess;
@@ -170,10 +166,13 @@ hipError_t launch_update(int, int nc, int, const StepArgs& a, bool fields, hipSt
 }
 hipError_t launch_init(int, int, int, const InitArgs&, hipStream_t) { return record("init"); }
 hipError_t launch_batch_step(int, int, int, const BatchLaunch& b, hipStream_t) {
-  return record("batch", b.args);
+  record("batch", b.args);
+  std::lock_guard<std::mutex> lk(fake::mx);
+  state().launches.back().shape.blocks = b.blocks_update;
+  return hipSuccess;
 }
 hipError_t launch_expand(int, int, int, const StepArgs&, hipStream_t) { return record("expand"); }
-int groups_per_cu(int, int, int, const StepArgs&, bool) { return 0; }
+int groups_per_cu(int, int, int, const StepArgs&, bool) { return state().groups_per_cu; }
 size_t conc_m_lds_bytes(int, int, int, int, bool) { return 32 << 10; }
 hipError_t launch_expand_f(int, int, const StepArgs&, void*, hipStream_t) { return record("expand_f"); }
 hipError_t launch_diag(int, int, int, const StepArgs&, int, double*, int* blocks, hipStream_t) {

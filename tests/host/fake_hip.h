@@ -27,7 +27,7 @@ struct State {
   long long events = 0;                     // live events
   size_t fail_at = 0;                       // a hipMalloc of this size fails
   bool pinned_fails = false;                // hipHostMalloc fails
-  bool capturing = false;                   // hipStreamIsCapturing
+  int groups_per_cu = 0;                    // occupancy of every kernel (0: not known)
 
   size_t device_bytes() const {
     size_t b = 0;

@@ -363,6 +363,40 @@ static void mobility_shapes() {
   CHECK(four_steps(480, 480, 4, NFLBM_FP32, 0.05, flags).nsteps == 2);
 }
 
+// The z runs of a batch fill the workgroup slots over all members, also where
+// each alone would take long ones; a run that was set stays.
+static void batch_runs_share_the_slots() {
+  state().groups_per_cu = 3;
+  Problem p(NFLBM_D3Q19, 137, 78, 179, 5, NFLBM_FP32), q(NFLBM_D3Q19, 60, 40, 30, 5, NFLBM_FP32);
+  const long long slots = 3 * 256;
+  for (int count : {1, 2, 3, 5, 8}) {
+    std::vector<nflbm_config> cfgs(count, p.cfg);
+    cfgs.push_back(q.cfg);
+    nflbm_batch* b = nullptr;
+    CHECK(nflbm_batch_create(cfgs.data(), int(cfgs.size()), &b) == NFLBM_OK);
+    int tx = 0;
+    CHECK(nflbm_batch_get_launch(b, &tx, nullptr, nullptr) == NFLBM_OK && tx == 6);
+    CHECK(nflbm_batch_step(b, 1, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+    const fake::Launch l = state().launches.back();
+    const long long tiles = count * 3LL * 20, small = 10;
+    long long best = 0;
+    for (int zc = 1; zc <= 179; ++zc) {
+      const long long groups = tiles * ((179 + zc - 1) / zc) + small * ((30 + zc - 1) / zc);
+      const long long cost = (groups + slots - 1) / slots * (zc + 2);
+      if (zc == 1 || cost < best) best = cost;
+    }
+    CHECK((l.shape.blocks + slots - 1) / slots * (l.step.zchunk + 2) == best);
+    nflbm_batch_destroy(b);
+  }
+  nflbm_config cfgs[2] = {p.cfg, p.cfg};
+  nflbm_batch* b = nullptr;
+  CHECK(nflbm_batch_create(cfgs, 2, &b) == NFLBM_OK);
+  CHECK(nflbm_set_launch(nflbm_batch_member(b, 0), 6, 7) == NFLBM_OK);
+  CHECK(nflbm_batch_step(b, 1, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+  CHECK(state().launches.back().step.zchunk == 7);
+  nflbm_batch_destroy(b);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -376,6 +410,7 @@ int main(int argc, char** argv) {
   else if (name == "batch_shares_the_form_of_f") batch_shares_the_form_of_f();
   else if (name == "fused_shapes") fused_shapes();
   else if (name == "mobility_shapes") mobility_shapes();
+  else if (name == "batch_runs_share_the_slots") batch_runs_share_the_slots();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

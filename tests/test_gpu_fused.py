@@ -290,3 +290,36 @@ def test_fused_mobility_tall_tiles():
     b.step(2)
     b.step(3)
     assert np.array_equal(a.get_state(), b.get_state())
+
+
+@pytest.mark.parametrize("N,precision", [(3, "fp32"), (6, "fp64"), (4, "fp16s")])
+def test_batch_member_gains_and_loses_solid_nodes(N, precision):
+    """A batch leaves the fused steps while a member has solid nodes and takes
+    them again afterwards, at the state its members have by then."""
+    shapes = [(64, 41), (90, 57)]
+    cfgs = [_config(s, N, precision) for s in shapes]
+    batch = nf.Batch(cfgs)
+    sims = [nf.Simulation(**c) for c in cfgs]
+    solid = np.zeros((1, 57, 90), dtype=bool)
+    solid[0, 20:30, 10:25] = True
+    for i, s in enumerate(shapes):
+        batch.set_fields(i, _noise(s, N, i))
+        sims[i].set_fields(_noise(s, N, i))
+
+    def advance(n):
+        batch.step(n)
+        for s in sims:
+            for _ in range(n):
+                s.step(1)
+
+    advance(6)
+    for mask in (solid, None, solid, None):
+        batch.members[1].set_solid(mask)
+        sims[1].set_solid(mask)
+        advance(5)
+        batch.members[0].step(3)         # one member on its own in between
+        for _ in range(3):
+            sims[0].step(1)
+        advance(4)
+    for m, s in zip(batch.members, sims):
+        _same(m, s)
