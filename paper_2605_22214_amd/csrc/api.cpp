@@ -638,9 +638,11 @@ int launch_step(nflbm_sim* s, hipEvent_t ev0, hipEvent_t ev1, bool* checked = nu
 
 // ------------------------------------------------- fused D2Q9 steps
 // Shape of the fused launches: LDS rows of 1 << wlog2 positions, up to T
-// steps a launch, tiles of h rows.
+// steps a launch, tiles of h rows; least: the (even) steps from which they are
+// taken.
 struct FusedPlan {
   int wlog2, T, h, threads;
+  int least = 2;
 };
 
 size_t fused_lds(const nflbm_sim* s, const FusedPlan& p) {
@@ -702,7 +704,13 @@ bool fused_plan(const nflbm_sim* const* m, size_t count, FusedPlan* out) {
   // potential force, whose arithmetic the halo repeats as well.
   bool options = false;
   for (size_t i = 0; i < count; ++i) options = options || (m[i]->step_flags & (kFlagOmega | kFlagPotential));
-  if (f64 ? N <= 4 : N <= 3) return take({5, 2, 24, 1024});
+  // Two or three steps are one a launch, each with its loads and stores of the
+  // records: there the two kernels win in FP64 and from N = 5 in float, at N = 4
+  // with the options (calls of 2 at 1000 x 1010, us a step: FP64 N = 5 71 by
+  // the two kernels, 87 fused; FP32 N = 5 with the options 45, 51; FP32 N = 3
+  // 24, 19).
+  const int least = f64 || N >= 5 || (N == 4 && options) ? 4 : 2;
+  if (f64 ? N <= 4 : N <= 3) return take({5, 2, 24, 1024, least});
   // From there on tiles as tall as LDS holds, in float twice a CU: one float
   // workgroup of 512 threads a CU leaves its SIMDs two wavefronts each (N = 5
   // at 700 x 650, FP16S: tiles of 24 x 24 22.4 us, of 24 x 20 14.8 us, the two
@@ -723,11 +731,11 @@ bool fused_plan(const nflbm_sim* const* m, size_t count, FusedPlan* out) {
   // still pays there (370 x 370 FP16S N = 7: 13.4, 10.8), at N = 8 without the
   // options.
   if (!f64 && (N == 8 || (N == 7 && (half || options)) || (N == 5 && half && options))) {
-    const FusedPlan p = tallest({5, 2, 24, 512}, 1);
+    const FusedPlan p = tallest({5, 2, 24, 512, least}, 1);
     return (N < 8 || !options) && fits(p, 1) && tiles(p) <= 256 && take(p);
   }
   const size_t groups = f64 ? 1 : 2;
-  FusedPlan p = tallest({5, 2, 24, f64 && (N == 5 || (N == 6 && !options)) ? 768 : 512}, groups);
+  FusedPlan p = tallest({5, 2, 24, f64 && (N == 5 || (N == 6 && !options)) ? 768 : 512, least}, groups);
   if (!fits(p, groups)) return false;
   const long long slots = 256LL * static_cast<long long>(groups);
   auto rounds = [&](const FusedPlan& q) { return (tiles(q) + slots - 1) / slots; };
@@ -900,7 +908,7 @@ int run_steps(nflbm_sim* s, long long n, bool* checked) {
   FusedPlan p;
   size_t lds = 0;
   if (n >= 2 && fused_mob_now(s) && fused_mob_plan(s, &p, &lds)) return run_mob_steps(s, n, p, lds, checked);
-  if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p)) {
+  if (n >= 2 && fused_now(s) && fused_plan(&s, 1, &p) && n >= p.least) {
     if (n & 1) {      // one by the two kernels, for the parity of C's sets
       const int rc = launch_step(s, nullptr, nullptr, checked);
       if (rc != NFLBM_OK) return rc;
@@ -1468,7 +1476,8 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode, bool fuse = true) {
   int rc = batch_half(b, &half);
   if (rc != NFLBM_OK) return rc;
   FusedPlan p;
-  if (fuse && nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p)) {
+  if (fuse && nsteps >= 2 && b->blocks_fused && fused_batch(b) && fused_plan(b->members.data(), b->members.size(), &p) &&
+      nsteps >= p.least) {
     bool given = false;
     for (const nflbm_sim* m : b->members) given = given || m->vel_given;
     if (given) {      // this step reads the velocities (see fused_now)

@@ -397,6 +397,28 @@ static void batch_runs_share_the_slots() {
   nflbm_batch_destroy(b);
 }
 
+// Calls of two and three steps beyond one round: one step a launch, where that
+// measured faster than the two kernels.
+static void short_calls() {
+  for (int precision : {NFLBM_FP64, NFLBM_FP32, NFLBM_FP16S})
+    for (int N = 2; N <= 8; ++N)
+      for (int side : {90, 1000}) {
+        Problem p(NFLBM_D2Q9, side, side, 1, N, precision);
+        nflbm_sim* s = make(p);
+        nflbm_batch* b = nullptr;
+        CHECK(nflbm_batch_create(&p.cfg, 1, &b) == NFLBM_OK);
+        CHECK(nflbm_step(s, 1) == NFLBM_OK && nflbm_batch_step(b, 1, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+        const bool few = side == 90 || (precision != NFLBM_FP64 && N <= 4);
+        for (int n : {2, 3}) {
+          state().launches.clear();
+          CHECK(nflbm_step(s, n) == NFLBM_OK && nflbm_batch_step(b, n, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+          CHECK(state().count("fused2d") == (few ? 2 : 0) && state().count("fused2d_batch") == (few ? 2 : 0));
+        }
+        nflbm_destroy(s);
+        nflbm_batch_destroy(b);
+      }
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -411,6 +433,7 @@ int main(int argc, char** argv) {
   else if (name == "fused_shapes") fused_shapes();
   else if (name == "mobility_shapes") mobility_shapes();
   else if (name == "batch_runs_share_the_slots") batch_runs_share_the_slots();
+  else if (name == "short_calls") short_calls();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

@@ -16,7 +16,8 @@ CHECKS = ["restored_velocities", "state_parity", "stepping_allocates_nothing", "
           "batch_autotune_times_its_kernels", "autotune_warms_its_kernels",
           "readback_without_pinned_memory", "readback_from_two_threads", "solid_memory",
           "batch_shares_the_form_of_f", "fused_shapes",
-          "mobility_shapes", "batch_runs_share_the_slots"]
+          "mobility_shapes", "batch_runs_share_the_slots",
+          "short_calls"]
 
 
 @pytest.fixture(scope="module")
