@@ -151,8 +151,9 @@ def run_form(nf, w, form, steps, warmup, timing_steps):
 def run_batch(nf, count, steps, per_sim_steps, seed=0):
     """Batch of independent D2Q9 N=3 lens / Janus problems (sides 64..512 in
     steps of 32, sigma_13 and sigma_23 drawn from U[0.0025, 0.01]), FP32
-    storage: graph replay of whole-batch steps against each member's own
-    launch sequence.  MLUPS counts the nodes of all members."""
+    storage: whole-batch steps (the library's graph mode, in which these
+    members take two steps a launch and no graph is replayed) against each
+    member's own launch sequence.  MLUPS counts the nodes of all members."""
     import workloads as W
     ws = W.batch_members(count=count, seed=seed)
     b = nf.Batch.from_workloads(ws, precision=nf.FP32)
@@ -182,8 +183,9 @@ def run_variants(nf, side, steps, warmup=20):
     lattice, N = 4, C_i from U[0, 2/N] renormalised (seed 0), FP32 storage:
     the constant mobility (m = 1/50, g in the moment form) and the
     concentration-dependent mobility of Appendix C (m* = 10, populations).
-    MLUPS over `steps` timed steps; bytes per node are the library's count of
-    what one step's kernels read and write."""
+    MLUPS over `steps` timed steps.  They are taken several a launch, with
+    the intermediate steps in LDS, so no bandwidth is derived from the library's
+    count of what a separate step's kernels read and write."""
     import torch
     import workloads as W
     out = {}
@@ -198,18 +200,16 @@ def run_variants(nf, side, steps, warmup=20):
             sim.step(steps)
             torch.cuda.synchronize()
             wall = time.perf_counter() - t0
-            bpn = sim.bytes_per_node()
             form = sim.storage_form()
         mlups = side * side * steps / wall / 1e6
-        out[name] = {"mlups": mlups, "ms_per_step": wall / steps * 1e3, "storage_of_g": form,
-                     "bytes_per_node": bpn, "step_gbs": mlups * 1e6 * bpn / 1e9}
+        out[name] = {"mlups": mlups, "ms_per_step": wall / steps * 1e3, "storage_of_g": form}
     out["workload"] = f"D2Q9 N=4 {side}^2 periodic, U[0, 2/N] mixture, diffusive-only, FP32"
     return out
 
 
 def run_small_configs(nf, steps, warmup=20):
     """Throughput of the smaller workloads of the parity tests, each stepped
-    alone on the GPU with the default launch (launch-bound at these sizes):
+    alone on the GPU as the library takes its steps (launch-bound at these sizes):
     the 64^2 liquid lens (D2Q9, N = 3, FP64), the 512^2 quaternary phase
     separation (D2Q9, N = 4, FP64 and FP32) and the 16 x 16 x 192 layered
     channel (D3Q19, N = 6, walls on z, FP32)."""
@@ -353,7 +353,7 @@ def main():
     if args.batch_count > 0:
         print(f"bench: batch of {args.batch_count} D2Q9 problems", file=sys.stderr, flush=True)
         batch = run_batch(nf, args.batch_count, args.batch_steps, max(2, args.batch_steps // 10))
-        print(f"bench: batch {batch['graph_mlups']:.0f} MLUPS (graph) vs {batch['per_sim_mlups']:.0f} "
+        print(f"bench: batch {batch['graph_mlups']:.0f} MLUPS vs {batch['per_sim_mlups']:.0f} "
               "(per simulation)", file=sys.stderr, flush=True)
     variants = None
     if args.variant_side > 0:

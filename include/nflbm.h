@@ -306,13 +306,18 @@ int nflbm_set_fields(nflbm_sim *sim, const double *C, const double *v, const dou
 /* Advance nsteps time steps (Sec. III: collide, stream, boundaries), each one
  * a reconstruction of C and one fused update launch on the sim's stream.
  * Calls of two and more steps of a periodic D2Q9 lattice without solid nodes
- * take several steps a launch where g and f are node records, where g is and
- * f is not evolved, or where f is not evolved, every tau_g = 1 and the mobility
- * depends on the concentrations; results do not depend on it.
+ * take up to four steps a launch where g and f are node records, where g is
+ * and f is not evolved, or where f is not evolved, every tau_g = 1 and the
+ * mobility depends on the concentrations, except in the forms and sizes in
+ * which the separate kernels measured faster (mostly N >= 5 in float on
+ * large lattices).  Results do not depend on it.  The first step after
+ * nflbm_set_fields, the odd step of an odd call and the first step of a
+ * diffusive-only run after nflbm_set_state are separate ones.
  * Asynchronous: returns after queueing the work, without waiting for it, and
- * allocates nothing.  Captured into a graph, an even number of steps advances
- * the state by as many on every replay, as long as the steps taken between
- * replays add up to an even number.
+ * allocates nothing.  Captured into a graph (with nflbm_set_nan_check at 0), an
+ * even number of steps advances the state by as many on every replay, as long
+ * as the steps taken between replays add up to an even number and no state is
+ * set in between.
  * NaN detection: on every K-th step (nflbm_set_nan_check, default K = 16)
  * the update raises a device flag where a node's C, mu~, v or P is not
  * finite, and nflbm_step queues a copy of that flag to host memory behind
@@ -336,13 +341,16 @@ int nflbm_set_nan_check(nflbm_sim *sim, long long every);
 /* Advance nsteps and return, through *ms, the elapsed device time measured
  * with HIP events recorded on the sim's stream around the launches; if
  * ms_update is not NULL also time each update launch separately (events
- * around every update kernel) and return their summed duration.
- * Synchronises; ENUMERIC as nflbm_synchronize. */
+ * around every update kernel) and return their summed duration.  With
+ * ms_update every step is a separate one, without it the steps are taken as
+ * nflbm_step takes them, several a launch where that applies: *ms of the two
+ * differs there.  Synchronises; ENUMERIC as nflbm_synchronize. */
 int nflbm_step_timed(nflbm_sim *sim, long long nsteps, double *ms, double *ms_update);
 
 /* Advance nsteps and return the summed durations of the reconstruction
  * launches (*ms_conc) and of the update launches (*ms_update), each measured
- * with HIP events recorded on the sim's stream right around the launch.
+ * with HIP events recorded on the sim's stream right around the launch; every
+ * step is a separate one.
  * Synchronises; ENUMERIC as nflbm_synchronize. */
 int nflbm_step_timed_kernels(nflbm_sim *sim, long long nsteps, double *ms_conc, double *ms_update);
 
@@ -432,7 +440,8 @@ int nflbm_coefficients(int N, const double *sigma, double D, double *alpha, doub
  * workgroup marches through zchunk planes (1 = a single plane) keeping three
  * planes of concentrations in LDS.  A value <= 0 keeps the current setting.
  * EINVAL if the shape is invalid or its LDS window exceeds the device limit.
- * Results do not depend on the shape, and steps taken several a launch
+ * Results do not depend on the shape (the FP64 sums of the diagnostics in
+ * their last bits: it groups their terms), and steps taken several a launch
  * (nflbm_step) have tiles of their own.  nflbm_get_launch also reports the
  * device's LDS bytes per workgroup (any output pointer may be NULL).  The
  * default shape (chosen at nflbm_create, and again by nflbm_set_solid until
@@ -457,7 +466,8 @@ int nflbm_storage_form(const nflbm_sim *sim);
  * EINVAL for NULL. */
 int nflbm_f_storage_form(const nflbm_sim *sim);
 
-/* Bytes moved per lattice-node update by the kernels of one step together,
+/* Bytes moved per lattice-node update by the kernels of one separate step
+ * together (steps taken several a launch, see nflbm_step, move fewer),
  * counting every stored population once read and once written plus the
  * reconstructed concentrations (written once, read once); f is left out of a
  * diffusive-only run (it is neither read nor written), and the
@@ -483,9 +493,13 @@ int nflbm_autotune(nflbm_sim *sim, const char *cache_path);
  * Batches: many independent simulations (each a full problem statement of
  * Secs. II-III with its own size, walls, tensions, relaxation times and
  * mobility) that share lattice, ncomp and precision, advanced together.
- * Every time step of the whole batch is two kernel launches whose workgroups
+ * A time step of the whole batch is two kernel launches whose workgroups
  * cover the tiles of all members; NFLBM_BATCH_GRAPH replays runs of
- * graph_steps such steps from a captured HIP graph.  Each member is an
+ * graph_steps such steps from a captured HIP graph.  Where every member is one
+ * that nflbm_step takes several steps a launch with (other than by the
+ * concentration-dependent mobility), all in the same form and without solid
+ * nodes, so does the batch, in one launch over all members, in both modes and
+ * without a graph.  Each member is an
  * nflbm_sim owned by the batch: nflbm_batch_member returns it for set_fields,
  * get_field, diagnostics, state I/O, solid nodes, open faces, the outflow
  * face or stepping on its own (never nflbm_destroy it).  A member with an
@@ -498,8 +512,8 @@ typedef struct nflbm_batch nflbm_batch; /* opaque */
 
 /* Stepping modes. */
 enum {
-  NFLBM_BATCH_LAUNCH = 0,  /* two launches per step for the whole batch          */
-  NFLBM_BATCH_GRAPH = 1,   /* the same launches replayed from a HIP graph         */
+  NFLBM_BATCH_LAUNCH = 0,  /* the batch's launches queued one by one             */
+  NFLBM_BATCH_GRAPH = 1,   /* steps of two launches replayed from a HIP graph     */
   NFLBM_BATCH_PER_SIM = 2  /* each member's own launch sequence, one after another
                               (the reference point the batch is measured against) */
 };
@@ -532,9 +546,12 @@ int nflbm_batch_step(nflbm_batch *b, long long nsteps, int mode);
 /* As nflbm_batch_step, returning in *ms the device time between HIP events
  * recorded on the batch stream before and after.  Synchronises. */
 int nflbm_batch_step_timed(nflbm_batch *b, long long nsteps, int mode, double *ms);
-/* Tile width 2^tx_log2 (4 or 6) used for every member in the batch launches,
- * and steps per captured graph (even, >= 2); values <= 0 keep the current
- * setting.  Discards captured graphs when the shape changes.  Synchronises. */
+/* Tile width 2^tx_log2 (4 or 6) used for every member in the two-kernel batch
+ * launches, and steps per captured graph (even, >= 2); values <= 0 keep the
+ * current setting.  Neither bears on steps taken several a launch.  In D3Q19
+ * with f as node records the z run is fitted over all members, but for members
+ * whose own was set (nflbm_set_launch, nflbm_autotune).  Discards captured
+ * graphs when the shape changes.  Synchronises. */
 int nflbm_batch_set_launch(nflbm_batch *b, int tx_log2, int graph_steps);
 int nflbm_batch_get_launch(nflbm_batch *b, int *tx_log2, int *graph_steps, int *blocks_update);
 /* Total lattice nodes over all members. */
