@@ -8,14 +8,16 @@
 // and records are rounded to their storage type after every step, so a run
 // does not depend on how its steps are split over the two paths.
 //
-// Float runs that fill the chip are bound by vector-ALU issue (82% busy over
-// 1740 x 1740, N = 3: 172 instructions of the reconstruction and 135 of the
-// update a node, times 1.6 for the halo and the lanes beyond a shrinking row),
-// FP64 at N = 6 by latency at three wavefronts a SIMD, small lattices by the
-// latency of the launch and of its phases.  Per step, two kernels against this
-// one: 64 x 64 FP64 N = 3 7.8 -> 3.0 us, nine 300 x 150 lenses FP64 N = 6
-// 61 -> 39 us, 32 lenses FP32 N = 3 (3.0 M nodes) 97 -> 61 us, 512 x 512 FP32
-// N = 4 10.1 -> 8.7 us, 2048 x 2048 FP32 N = 4 without the flow 88 -> 32 us.
+// Float runs that fill the chip are bound by vector-ALU issue (75% of its peak
+// and LDS busy 48% of the time over 32 lenses of 3.0 M nodes, N = 3: 602
+// instructions a node and step with those of the halo and of the lanes beyond
+// a shrinking row), FP64 at N = 6 by latency at 2.2 wavefronts a SIMD (VALU
+// 32%, LDS 23%), small lattices by the latency of the launch and of its phases.
+// Per step, two kernels against this one: 64 x 64 FP64 N = 3 7.8 -> 3.0 us, nine
+// 300 x 150 lenses FP64 N = 6 61 -> 39 us, those 32 lenses 97 -> 61 us, 512 x
+// 512 FP32 N = 4 10.1 -> 8.7 us, 2048 x 2048 FP32 N = 4 without the flow 88 ->
+// 32 us.  From N = 5 on the halo's arithmetic can cost more than the launches
+// and the memory round trips it saves: fused_plan (api.cpp) draws that line.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
