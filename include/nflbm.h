@@ -242,7 +242,7 @@ int nflbm_set_stream(nflbm_sim *sim, void *hip_stream);
  * plane only at solid nodes (ENOTSUP otherwise: set the solid nodes first).
  * ENOTSUP with the concentration-dependent mobility.  Call before
  * nflbm_set_fields.  EINVAL for a bad face, an unwalled axis, the outflow
- * face, non-finite values or C_b not summing to 1. */
+ * face, non-finite values or C_b not summing to 1.  Synchronises. */
 int nflbm_set_open_face(nflbm_sim *sim, int face, const double *v_b, const double *C_b);
 
 /* Convective outflow (Sec. III C, Eq. convect): turns the wall face `face`

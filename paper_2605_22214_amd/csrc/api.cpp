@@ -1846,6 +1846,8 @@ int upload_faces(nflbm_sim* sim) {
     sim->faces = nullptr;
     return fail(sim, NFLBM_ENOMEM, "cannot allocate the open-face table");
   }
+  // the copy below does not wait for steps queued on a stream of the caller's
+  HIPCHK(sim, hipStreamSynchronize(sim->stream));
   hipError_t e;
   if (sim->ts == 8) {
     auto* t = new FaceBC<double>();

@@ -51,6 +51,7 @@ hipError_t hipHostFree(void* p) {
   return hipSuccess;
 }
 hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+  state().copied_after = state().syncs;
   std::memcpy(d, s, n);
   return hipSuccess;
 }

@@ -24,6 +24,7 @@ struct State {
   std::vector<Launch> launches;
   std::map<void*, size_t> device, pinned;   // live allocations
   long long mallocs = 0, syncs = 0;         // hipMalloc and hipStreamSynchronize calls
+  long long copied_after = 0;               // the waits before the last hipMemcpy
   long long events = 0;                     // live events
   size_t fail_at = 0;                       // a hipMalloc of this size fails
   bool pinned_fails = false;                // hipHostMalloc fails

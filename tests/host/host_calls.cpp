@@ -419,6 +419,23 @@ static void short_calls() {
       }
 }
 
+// The table of the open faces is replaced by a copy on the default stream,
+// which does not wait for steps queued on the simulation's: the call does.
+static void open_faces_wait_for_queued_steps() {
+  Problem p(NFLBM_D3Q19, 20, 12, 10, 3, NFLBM_FP32);
+  p.cfg.wall[0] = 1;
+  nflbm_sim* s = make(p);
+  const double v[3] = {0.01, 0.0, 0.0}, c[3] = {0.5, 0.25, 0.25};
+  CHECK(nflbm_set_open_face(s, 0, v, c) == NFLBM_OK && nflbm_set_open_face(s, 1, v, c) == NFLBM_OK);
+  for (bool open : {true, false}) {
+    CHECK(nflbm_step(s, 3) == NFLBM_OK);
+    const long long waits = state().syncs;
+    CHECK(nflbm_set_open_face(s, 0, open ? v : nullptr, open ? c : nullptr) == NFLBM_OK);
+    CHECK(state().copied_after > waits);
+  }
+  nflbm_destroy(s);
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -434,6 +451,7 @@ int main(int argc, char** argv) {
   else if (name == "mobility_shapes") mobility_shapes();
   else if (name == "batch_runs_share_the_slots") batch_runs_share_the_slots();
   else if (name == "short_calls") short_calls();
+  else if (name == "open_faces_wait_for_queued_steps") open_faces_wait_for_queued_steps();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

@@ -152,3 +152,32 @@ def test_open_face_argument_errors():
             sim.set_open_face(3, (1e-3, 0, 0), (0.7, 0.2))                 # sum != 1
         sim.set_open_face(3, (1e-3, 0, 0), (1.0, 0.0))
         sim.set_open_face(3)                                               # a wall again
+
+
+def test_faces_change_behind_queued_steps():
+    """Steps queued on a stream of the caller's end with the faces they were
+    queued with."""
+    torch = pytest.importorskip("torch")
+    shape, N = (96, 64, 48), 3
+    C = 1.0 / N + np.random.default_rng(9).uniform(-0.1, 0.1, size=(N,) + shape[::-1])
+    C /= C.sum(axis=0)
+    sims = []
+    for _ in range(2):
+        s = nf.Simulation("D3Q19", shape, equal_sigma(N, 0.01), np.ones(N), m=0.05, precision="fp32",
+                          walls=(True, False, True))
+        for face in (0, 4):
+            v = [0.0, 0.0, 0.0]
+            v[face // 2] = 0.004
+            s.set_open_face(face, v, np.full(N, 1.0 / N))
+        s.set_fields(C)
+        sims.append(s)
+    stream = torch.cuda.Stream()
+    sims[1].set_stream(stream.cuda_stream)
+    for s, wait in zip(sims, (True, False)):
+        for face, v in ((0, (0.01, 0.0, 0.0)), (4, None), (4, (0.0, 0.0, -0.002))):
+            s.step(60)
+            if wait:
+                s.synchronize()
+            s.set_open_face(face, v, None if v is None else np.full(N, 1.0 / N))
+        s.step(60)
+    assert np.array_equal(sims[0].get_state(), sims[1].get_state())
