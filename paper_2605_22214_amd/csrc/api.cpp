@@ -185,6 +185,7 @@ struct nflbm_batch {
   int blocks_fused = 0;
   std::vector<int> key;     // member parities that args[0..count) was built for
   std::vector<unsigned> versions;   // members' boundary_version at that build
+  bool local = false;       // some member's arguments are those of its first step
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
   // NaN flag shared by the members' batch steps, which check every step
@@ -1266,6 +1267,7 @@ int build_batch_tables(nflbm_batch* b, bool new_shape) {
   std::vector<StepArgs> args(2 * size_t(count));
   b->key.assign(count, 0);
   b->versions.assign(count, 0u);
+  b->local = false;
   // one kernel variant for all members: the wall variant if any needs it
   b->walls = 0;
   for (const nflbm_sim* m : b->members)
@@ -1275,6 +1277,7 @@ int build_batch_tables(nflbm_batch* b, bool new_shape) {
     const nflbm_sim* m = b->members[i];
     b->key[i] = m->cur;
     b->versions[i] = m->boundary_version;
+    b->local = b->local || m->f_local;
     args[i] = batch_args(b, m, m->cur);
     args[count + i] = batch_args(b, m, m->cur ^ 1);
     for (StepArgs* x : {&args[i], &args[count + i]}) {
@@ -1471,6 +1474,11 @@ int batch_run(nflbm_batch* b, long long nsteps, int mode, bool fuse = true) {
       return NFLBM_OK;
     }
     return batch_run(b, nsteps - 1, mode, fuse);
+  }
+  if (b->local && nsteps > 0) {
+    // the members took their first step on their own, or were given a state
+    const int rc = build_batch_tables(b, false);
+    if (rc != NFLBM_OK) return rc;
   }
   int half = 0;
   int rc = batch_half(b, &half);

@@ -436,6 +436,34 @@ static void open_faces_wait_for_queued_steps() {
   nflbm_destroy(s);
 }
 
+// The first step after set_fields takes f from each node's own record; batch
+// steps after it do not, also where the members took it on their own or were
+// given a state.
+static void batch_after_members_stepped() {
+  for (int lattice : {int(NFLBM_D2Q9), int(NFLBM_D3Q19)}) {
+    Problem p(lattice, 20, 18, lattice == NFLBM_D2Q9 ? 1 : 9, 3, NFLBM_FP32);
+    std::vector<unsigned char> raw;
+    for (int how = 0; how < 3; ++how) {
+      nflbm_batch* b = nullptr;
+      CHECK(nflbm_batch_create(&p.cfg, 1, &b) == NFLBM_OK);
+      nflbm_sim* m = nflbm_batch_member(b, 0);
+      if (how == 0) CHECK(nflbm_batch_step(b, 2, NFLBM_BATCH_PER_SIM) == NFLBM_OK);
+      if (how == 1) CHECK(nflbm_step(m, 3) == NFLBM_OK);
+      if (how == 2) CHECK(nflbm_set_state(m, raw.data()) == NFLBM_OK);
+      for (int i = 0; i < 3; ++i) {
+        CHECK(nflbm_batch_step(b, 1, NFLBM_BATCH_LAUNCH) == NFLBM_OK);
+        CHECK(state().launches.back().kind == "batch");
+        CHECK(!(state().launches.back().step.flags & nflbm::kFlagFLocal));
+      }
+      size_t bytes = 0;
+      CHECK(nflbm_state_bytes(m, &bytes) == NFLBM_OK);
+      raw.resize(bytes);
+      CHECK(nflbm_get_state(m, raw.data()) == NFLBM_OK);
+      nflbm_batch_destroy(b);
+    }
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   if (name == "restored_velocities") restored_velocities();
@@ -452,6 +480,7 @@ int main(int argc, char** argv) {
   else if (name == "batch_runs_share_the_slots") batch_runs_share_the_slots();
   else if (name == "short_calls") short_calls();
   else if (name == "open_faces_wait_for_queued_steps") open_faces_wait_for_queued_steps();
+  else if (name == "batch_after_members_stepped") batch_after_members_stepped();
   else if (name == "other_record_set") other_record_set();
   else {
     std::fprintf(stderr, "no check named '%s'\n", name.c_str());

@@ -245,3 +245,38 @@ def test_members_of_both_forms_of_f(lattice, shape, precision):
             assert member.f_storage_form() == "populations"
             s.step(7)
             assert np.array_equal(member.get_state(), s.get_state())
+
+
+@pytest.mark.parametrize("lattice,shape", [("D2Q9", (41, 30, 1)), ("D3Q19", (18, 11, 9))])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16s"])
+def test_batch_after_members_stepped_alone(lattice, shape, precision):
+    """Batch steps after the members' first steps on their own, or from a
+    restored state, without a batch step before."""
+    N = 3
+    cfg = dict(lattice=lattice, shape=shape, sigma=0.01 * (np.ones((N, N)) - np.eye(N)), tau=np.ones(N), m=0.05,
+               precision=precision, body_force=(1e-6, 0.0, 0.0))
+    C = 1.0 / N + np.random.default_rng(3).uniform(-0.1, 0.1, size=(N,) + shape[::-1])
+    C /= C.sum(axis=0)
+    with nf.Simulation(**cfg) as s:
+        s.set_fields(C)
+        s.step(4)
+        raw = s.get_state()
+        for _ in range(6):
+            s.step(1)
+        want = s.get_state()
+    for how in ("per_sim", "member", "state"):
+        for steps in ((6,), (1, 1, 4), (3, 3)):
+            with nf.Batch([cfg, cfg]) as batch:
+                for i, m in enumerate(batch.members):
+                    if how == "state":
+                        m.set_state(raw)
+                        continue
+                    batch.set_fields(i, C)
+                    if how == "member":
+                        m.step(4)
+                if how == "per_sim":
+                    batch.step(4, "per_sim")
+                for n in steps:
+                    batch.step(n, "launch")
+                for m in batch.members:
+                    assert np.array_equal(m.get_state(), want), (how, steps)

@@ -17,7 +17,8 @@ CHECKS = ["restored_velocities", "state_parity", "stepping_allocates_nothing", "
           "readback_without_pinned_memory", "readback_from_two_threads", "solid_memory",
           "batch_shares_the_form_of_f", "fused_shapes",
           "mobility_shapes", "batch_runs_share_the_slots",
-          "short_calls", "open_faces_wait_for_queued_steps"]
+          "short_calls", "open_faces_wait_for_queued_steps",
+          "batch_after_members_stepped"]
 
 
 @pytest.fixture(scope="module")
