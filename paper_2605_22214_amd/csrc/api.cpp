@@ -698,7 +698,7 @@ bool fused_plan(const nflbm_sim* const* m, size_t count, FusedPlan* out) {
   if (fits(medium, 1) && tiles(medium) <= (fits(medium, 2) ? 512 : 256)) return take(medium);
   // Without the flow the widest tiles from there on (1400 x 1400 FP32 N = 4:
   // 16.7 us, 18.2 with 24 x 24); until they fill the chip, near 580 x 580,
-  // smaller ones would do better (400 x 400: over 4.1 us, 3.4 with three steps
+  // smaller ones would do better (400 x 400: over 4.06 us, 3.4 with three steps
   // of 20 x 8), and both are faster than the two kernels.
   if (!s->fform) {
     for (const FusedPlan& p : {FusedPlan{6, 2, 24, 1024}, FusedPlan{5, 2, 16, 512}, medium})
